@@ -97,17 +97,14 @@ zp_status zp_create(zp_ctx **out);
 void zp_destroy(zp_ctx *ctx);
 const char *zp_last_error(const zp_ctx *ctx); /* ctx may be NULL: text of the last failed zp_create/zp_plan */
 
-/* Device scratch zp_score / zp_compress need beyond inputs and outputs for this shape.  The kernels of this build keep
-   everything between their steps on chip, so this is 0; it is non-zero only for the switched-off split kernel (see
-   ZP_OPT_SPLIT), whose exchange buffers the context would allocate on first use and keep. */
+/* Device scratch zp_score / zp_compress need beyond inputs and outputs for this shape.  The kernels keep everything between
+   their steps on chip, so this is 0. */
 size_t zp_scratch_bytes(const zp_pool *pool, const zp_batch *batch);
 
-/* Tuning / test switches.  ZP_OPT_SPLIT: -1 automatic (default) and 0 = one workgroup per unit (keys swept twice
-   from HBM).  1 = several workgroups per unit with LDS-resident key chunks (keys read from HBM once; needs the scratch
-   zp_scratch_bytes reports) is SWITCHED OFF in this build and returns ZP_EUNSUPPORTED: the bounded wait between the
-   workgroups of a unit has expired intermittently on MI355X and the cause is not established.
-   ZP_OPT_SPIN_LIMIT: bound on that wait loop (iterations, > 0).
-   ZP_OPT_STREAMS: cap (1..8) on the ticket streams the split path orders its workgroups by.
+/* Tuning / test switches.  ZP_OPT_SPLIT: -1 (default) and 0 are accepted and change nothing; 1 asked for a kernel in which
+   several workgroups of a unit wait for each other, whose bounded wait expired intermittently on MI355X without a cause
+   being established: it is not part of the library and the value returns ZP_EUNSUPPORTED.
+   ZP_OPT_SPIN_LIMIT (> 0), ZP_OPT_STREAMS (1..8): settings of that kernel, accepted without effect.
    ZP_OPT_XCD_MAP: 1 (default) = every XCD works on a contiguous range of units, so that the kv heads of one
    (request, layer), which read the same blocks, run side by side on one XCD; 0 = workgroup i takes unit i. */
 typedef enum { ZP_OPT_SPLIT = 1, ZP_OPT_SPIN_LIMIT = 2, ZP_OPT_STREAMS = 3, ZP_OPT_XCD_MAP = 4 } zp_option;

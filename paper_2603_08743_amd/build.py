@@ -9,8 +9,6 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libzp.so")
-# zp_split.hip / zp_split_d64.hip (several workgroups per unit) are not built: that path is switched off in the library
-# (zp_set_option refuses it); building them again takes -DZP_WITH_SPLIT on zp_api.hip as well.
 SOURCES = ["zp_mfma_d128.hip", "zp_mfma_d128_wide.hip", "zp_mfma_d64.hip", "zp_mfma_d64_wide.hip", "zp_kernels.hip", "zp_check.hip", "zp_api.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
