@@ -9,7 +9,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libzp.so")
-SOURCES = ["zp_mfma_d128.hip", "zp_mfma_d128_wide.hip", "zp_mfma_d64.hip", "zp_mfma_d64_wide.hip", "zp_kernels.hip", "zp_check.hip", "zp_api.hip"]
+SOURCES = ["zp_mfma_d128_wide_ref.hip", "zp_mfma_d128_ref.hip", "zp_mfma_d64_wide_ref.hip", "zp_mfma_d128_wide.hip", "zp_mfma_d64_ref.hip",
+           "zp_mfma_d128.hip", "zp_mfma_d64_wide.hip", "zp_mfma_d64.hip", "zp_mfma_pad_bf16.hip", "zp_mfma_pad_bf16_long.hip",
+           "zp_mfma_pad_f32.hip", "zp_kernels.hip", "zp_check.hip", "zp_api.hip"]       # the slowest to compile first
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
 
@@ -29,7 +31,7 @@ def build(verbose: bool = False) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES), 8)) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     tmp = LIB + ".tmp.%d" % os.getpid()
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], capture_output=True, text=True)

@@ -91,7 +91,7 @@ extern "C" zp_status zp_set_option(zp_ctx *ctx, int32_t option, int32_t value) {
 
 // Scalar checks shared by every call, and the kernel argument block.  `need_q`: the call scores.
 static zp_status prepare(zp_ctx *ctx, const char *who, const zp_pool *p, const zp_batch *b, bool need_q, zp::Args *a,
-                         Path *path, int *NW, int *RB, const zp_extras *ex = nullptr, bool fused = false) {
+                         Path *path, zp::MfmaGeo *geo, const zp_extras *ex = nullptr, bool fused = false) {
     if (!ctx) return fail(nullptr, ZP_EINVAL, "%s: ctx is NULL", who);
     if (!p || !b) return fail(ctx, ZP_EINVAL, "%s: pool or batch is NULL", who);
     if (p->dtype != ZP_F32 && p->dtype != ZP_BF16) return fail(ctx, ZP_EINVAL, "%s: unknown dtype %d", who, p->dtype);
@@ -129,15 +129,11 @@ static zp_status prepare(zp_ctx *ctx, const char *who, const zp_pool *p, const z
     a->xcd_map = ctx->xcd_map;
 
     *path = PATH_GENERIC;
-    *NW = 4; *RB = 0;
-    size_t score_bytes = (size_t)a->G * a->w * 4;
-    if (need_q && zp::mfma_path_available(*a, NW, RB)) {
+    *geo = zp::MfmaGeo{4, 0, 1, 0, false};
+    if (need_q && zp::mfma_path_available(*a, geo)) {
         *path = PATH_MFMA;
-        const int UL = 16 / a->G;
-        a->NB = (a->w + 2 * UL - 1) / (2 * UL);
-        score_bytes = zp::mfma_union_bytes(a->d, *NW, *NW * *RB);
+        a->NP = geo->NP;
     }
-    if (!need_q) score_bytes = 0;
     // score refinements (they run in the tail of the one-workgroup-per-unit kernels only)
     if (ex) {
         if (ex->pool_kernel < 1 || !(ex->pool_kernel & 1)) return fail(ctx, ZP_EINVAL, "%s: pool_kernel %d must be odd and >= 1", who, ex->pool_kernel);
@@ -153,22 +149,31 @@ static zp_status prepare(zp_ctx *ctx, const char *who, const zp_pool *p, const z
         a->inv_tau_log2 = ex->lambda != 0.f ? (float)(1.4426950408889634 / (double)ex->tau) : 0.f;
         a->pool_r = ex->pool_kernel / 2;
     }
-    const bool red_mfma = *path == PATH_MFMA && a->b_shift >= 0 && p->b <= 32;
-    if ((a->ex & zp::EX_RED) && *path == PATH_MFMA && p->b == 16 && *RB == 1) a->ex |= zp::EX_RED_FUSED;   // similarity tiles from sweep 2's key tiles
-    const size_t refine_bytes = !a->ex ? 0 : ((a->ex & (zp::EX_POOL | zp::EX_RED)) ? (size_t)a->T_max * 4 : 0) +
-                                ((a->ex & zp::EX_RED) ? (red_mfma ? (size_t)*NW * 96 * 4 : (size_t)a->T_max * 12) : 0);
-    const size_t list_bytes = (size_t)a->budget * 4;
-    const int misc_bytes = align16((int)sizeof(int) * (256 + 16 + 4));
-    a->off_S = 0;
-    a->off_tbl = align16(a->T_max * 4);
-    a->off_dst = a->off_tbl + align16(a->max_blocks * 4);
-    a->off_misc = a->off_dst + align16((a->N_max - 1) * 4);
-    a->off_union = a->off_misc + misc_bytes;
-    size_t union_bytes = score_bytes > list_bytes ? score_bytes : list_bytes;
-    if (refine_bytes > union_bytes) union_bytes = refine_bytes;
-    a->off_G = a->off_union + align16((int)union_bytes);
-    a->off_R = a->off_G + ((a->ex & zp::EX_MOVE_F_LDS) ? align16(a->T_max * 4) : 0);
-    const size_t total = (size_t)a->off_R + ((a->ex & zp::EX_RED_FUSED) ? (size_t)a->T_max * 4 + (size_t)*NW * 96 * 4 : 0);
+    // LDS of one unit; `worst`: as the fused call with a moved global-score cache would need it
+    auto layout = [&](bool worst) {
+        const bool mf = *path == PATH_MFMA, move_f = (a->ex & zp::EX_MOVE_F_LDS) || (worst && ex && ex->F && b->dst_table);
+        // similarity tiles from sweep 2's key tiles
+        if ((a->ex & zp::EX_RED) && mf && !geo->pad && p->b == 16 && geo->RB == 1) a->ex |= zp::EX_RED_FUSED;
+        const size_t score_bytes = !need_q ? 0 : mf ? zp::mfma_union_bytes(*geo) : (size_t)a->G * a->w * 4;
+        const size_t red_bytes = mf && 32 % p->b == 0 ? (size_t)geo->NW * 96 * 4 : (size_t)a->T_max * 12;
+        const size_t refine_bytes = ((a->ex & (zp::EX_POOL | zp::EX_RED)) ? (size_t)a->T_max * 4 : 0) + ((a->ex & zp::EX_RED) ? red_bytes : 0);
+        const size_t list_bytes = (size_t)a->budget * 4;
+        const int misc_bytes = align16((int)sizeof(int) * (256 + 16 + 4));
+        a->off_S = 0;
+        a->off_tbl = align16(a->T_max * 4);
+        a->off_dst = a->off_tbl + align16(a->max_blocks * 4);
+        a->off_misc = a->off_dst + align16((a->N_max - 1) * 4);
+        a->off_union = a->off_misc + misc_bytes;
+        size_t union_bytes = score_bytes > list_bytes ? score_bytes : list_bytes;
+        if (refine_bytes > union_bytes) union_bytes = refine_bytes;
+        a->off_G = a->off_union + align16((int)union_bytes);
+        a->off_R = a->off_G + (move_f ? align16(a->T_max * 4) : 0);
+        return (size_t)a->off_R + ((a->ex & zp::EX_RED_FUSED) ? (size_t)a->T_max * 4 + (size_t)geo->NW * 96 * 4 : 0);
+    };
+    // Sequences so long that their scores leave no room for key tiles of this row size go to the vector-ALU kernel (the
+    // staged and the fused call decide alike: they give the same bits).
+    if (*path == PATH_MFMA && geo->pad && layout(true) > (size_t)kLdsLimit) *path = PATH_GENERIC;
+    const size_t total = layout(false);
     if (total > (size_t)kLdsLimit)
         return fail(ctx, ZP_EUNSUPPORTED, "%s: %zu bytes of LDS per unit exceed %d (max_blocks*b too large)", who, total, kLdsLimit);
     a->lds_bytes = (int)align16((int)total);
@@ -180,65 +185,65 @@ extern "C" size_t zp_scratch_bytes(const zp_pool *pool, const zp_batch *batch) {
     return 0;
 }
 
-static zp_status launch(zp_ctx *ctx, const char *who, zp::Args &a, Path path, int NW, int RB, void *stream) {
+static zp_status launch(zp_ctx *ctx, const char *who, zp::Args &a, Path path, const zp::MfmaGeo &geo, void *stream) {
     const int units = a.B * a.L_slab * a.h_kv;
-    hipError_t e = path == PATH_MFMA ? zp::launch_unit_mfma(a, units, NW, RB, (hipStream_t)stream)
+    hipError_t e = path == PATH_MFMA ? zp::launch_unit_mfma(a, units, geo, (hipStream_t)stream)
                                      : zp::launch_unit_generic(a, units, (hipStream_t)stream);
     if (e != hipSuccess) return fail(ctx, ZP_EHIP, "%s: kernel launch failed: %s", who, hipGetErrorString(e));
     return ZP_OK;
 }
 
 extern "C" zp_status zp_score(zp_ctx *ctx, const zp_pool *pool, const zp_batch *batch, float *scores, void *stream) {
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(ctx, "zp_score", pool, batch, true, &a, &path, &NW, &RB);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(ctx, "zp_score", pool, batch, true, &a, &path, &geo);
     if (rc) return rc;
     if (!scores && batch->B > 0) return fail(ctx, ZP_EINVAL, "zp_score: scores is NULL");
     a.stages = zp::STAGE_SCORE;
     a.scores_out = scores;
-    return launch(ctx, "zp_score", a, path, NW, RB, stream);
+    return launch(ctx, "zp_score", a, path, geo, stream);
 }
 
 extern "C" zp_status zp_score_ex(zp_ctx *ctx, const zp_pool *pool, const zp_batch *batch, const zp_extras *extras, float *scores,
                                  void *stream) {
     if (!extras) return zp_score(ctx, pool, batch, scores, stream);
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(ctx, "zp_score_ex", pool, batch, true, &a, &path, &NW, &RB, extras, false);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(ctx, "zp_score_ex", pool, batch, true, &a, &path, &geo, extras, false);
     if (rc) return rc;
     if (!scores && batch->B > 0) return fail(ctx, ZP_EINVAL, "zp_score_ex: scores is NULL");
     a.stages = zp::STAGE_SCORE;
     a.scores_out = scores;
-    return launch(ctx, "zp_score_ex", a, path, NW, RB, stream);
+    return launch(ctx, "zp_score_ex", a, path, geo, stream);
 }
 
 extern "C" zp_status zp_select_topk(zp_ctx *ctx, const float *scores, int32_t T_max, const zp_pool *pool, const zp_batch *batch,
                                     int32_t *keep_idx, int32_t *len_out, void *stream) {
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(ctx, "zp_select_topk", pool, batch, false, &a, &path, &NW, &RB);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(ctx, "zp_select_topk", pool, batch, false, &a, &path, &geo);
     if (rc) return rc;
     if ((!scores || !keep_idx || !len_out) && batch->B > 0) return fail(ctx, ZP_EINVAL, "zp_select_topk: scores / keep_idx / len_out is NULL");
     if (T_max < a.T_max) return fail(ctx, ZP_EINVAL, "zp_select_topk: T_max %d smaller than max_blocks*b = %d", T_max, a.T_max);
     a.stages = zp::STAGE_LOAD_SCORES | zp::STAGE_SELECT;
     a.scores_in = scores; a.scores_in_stride = T_max;
     a.keep_idx_out = keep_idx; a.len_out = len_out;
-    return launch(ctx, "zp_select_topk", a, PATH_GENERIC, NW, RB, stream);
+    return launch(ctx, "zp_select_topk", a, PATH_GENERIC, geo, stream);
 }
 
 extern "C" zp_status zp_compact_kv(zp_ctx *ctx, const zp_pool *pool, const zp_batch *batch, const int32_t *keep_idx,
                                    const int32_t *len, void *stream) {
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(ctx, "zp_compact_kv", pool, batch, false, &a, &path, &NW, &RB);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(ctx, "zp_compact_kv", pool, batch, false, &a, &path, &geo);
     if (rc) return rc;
     if ((!keep_idx || !len) && batch->B > 0) return fail(ctx, ZP_EINVAL, "zp_compact_kv: keep_idx / len is NULL");
     a.stages = zp::STAGE_LOAD_LIST | zp::STAGE_COMPACT;
     a.keep_idx_in = keep_idx; a.len_in = len;
-    return launch(ctx, "zp_compact_kv", a, PATH_GENERIC, NW, RB, stream);
+    return launch(ctx, "zp_compact_kv", a, PATH_GENERIC, geo, stream);
 }
 
 extern "C" zp_status zp_compact_kv_ex(zp_ctx *ctx, const zp_pool *pool, const zp_batch *batch, float *F, const int32_t *keep_idx,
                                       const int32_t *len, void *stream) {
     if (!F) return zp_compact_kv(ctx, pool, batch, keep_idx, len, stream);
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(ctx, "zp_compact_kv_ex", pool, batch, false, &a, &path, &NW, &RB);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(ctx, "zp_compact_kv_ex", pool, batch, false, &a, &path, &geo);
     if (rc) return rc;
     if ((!keep_idx || !len) && batch->B > 0) return fail(ctx, ZP_EINVAL, "zp_compact_kv_ex: keep_idx / len is NULL");
     if ((long long)pool->L_slab * pool->N_total * pool->b * pool->h_kv > 0xffffffffLL)
@@ -246,30 +251,30 @@ extern "C" zp_status zp_compact_kv_ex(zp_ctx *ctx, const zp_pool *pool, const zp
     a.stages = zp::STAGE_LOAD_LIST | zp::STAGE_COMPACT;
     a.keep_idx_in = keep_idx; a.len_in = len;
     a.F = F; a.ex = zp::EX_MOVE_F;
-    return launch(ctx, "zp_compact_kv_ex", a, PATH_GENERIC, NW, RB, stream);
+    return launch(ctx, "zp_compact_kv_ex", a, PATH_GENERIC, geo, stream);
 }
 
 extern "C" zp_status zp_compress_ex(zp_ctx *ctx, const zp_pool *pool, const zp_batch *batch, const zp_extras *extras, int32_t *len_out,
                                     float *scores_dbg, int32_t *keep_idx_dbg, void *stream) {
     if (!extras) return zp_compress(ctx, pool, batch, len_out, scores_dbg, keep_idx_dbg, stream);
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(ctx, "zp_compress_ex", pool, batch, true, &a, &path, &NW, &RB, extras, true);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(ctx, "zp_compress_ex", pool, batch, true, &a, &path, &geo, extras, true);
     if (rc) return rc;
     if (!len_out && batch->B > 0) return fail(ctx, ZP_EINVAL, "zp_compress_ex: len_out is NULL");
     a.stages = zp::STAGE_SCORE | zp::STAGE_SELECT | zp::STAGE_COMPACT;
     a.scores_out = scores_dbg; a.keep_idx_out = keep_idx_dbg; a.len_out = len_out;
-    return launch(ctx, "zp_compress_ex", a, path, NW, RB, stream);
+    return launch(ctx, "zp_compress_ex", a, path, geo, stream);
 }
 
 extern "C" zp_status zp_compress(zp_ctx *ctx, const zp_pool *pool, const zp_batch *batch, int32_t *len_out, float *scores_dbg,
                                  int32_t *keep_idx_dbg, void *stream) {
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(ctx, "zp_compress", pool, batch, true, &a, &path, &NW, &RB);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(ctx, "zp_compress", pool, batch, true, &a, &path, &geo);
     if (rc) return rc;
     if (!len_out && batch->B > 0) return fail(ctx, ZP_EINVAL, "zp_compress: len_out is NULL");
     a.stages = zp::STAGE_SCORE | zp::STAGE_SELECT | zp::STAGE_COMPACT;
     a.scores_out = scores_dbg; a.keep_idx_out = keep_idx_dbg; a.len_out = len_out;
-    return launch(ctx, "zp_compress", a, path, NW, RB, stream);
+    return launch(ctx, "zp_compress", a, path, geo, stream);
 }
 
 // ------------------------------------------------------------------ entry point that allocates nothing
@@ -308,8 +313,8 @@ extern "C" zp_status zp_compress_static(const zp_pool *pool, const zp_batch *bat
     }
     zp_ctx tmp;                                               // host-side only: carries defaults and the error text
     tmp.device = dev; tmp.d_status = words; tmp.h_status = nullptr; tmp.xcd_map = 1; tmp.n_cu = 0; tmp.err[0] = 0;
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(&tmp, "zp_compress_static", pool, batch, true, &a, &path, &NW, &RB);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(&tmp, "zp_compress_static", pool, batch, true, &a, &path, &geo);
     if (rc == ZP_OK && !len_out && batch->B > 0) rc = fail(&tmp, ZP_EINVAL, "zp_compress_static: len_out is NULL");
     if (rc == ZP_OK && batch->B > 0) {
         a.stages = zp::STAGE_SCORE | zp::STAGE_SELECT | zp::STAGE_COMPACT;
@@ -319,7 +324,7 @@ extern "C" zp_status zp_compress_static(const zp_pool *pool, const zp_batch *bat
         hipLaunchKernelGGL(clear_words, dim3(1), dim3(64), 0, (hipStream_t)stream, words, 8);
         e = hipGetLastError();
         if (e != hipSuccess) rc = fail(&tmp, ZP_EHIP, "zp_compress_static: kernel launch failed: %s", hipGetErrorString(e));
-        else rc = launch(&tmp, "zp_compress_static", a, path, NW, RB, stream);
+        else rc = launch(&tmp, "zp_compress_static", a, path, geo, stream);
     }
     if (rc != ZP_OK) snprintf(g_err, sizeof(g_err), "%s", tmp.err);
     return rc;
@@ -364,8 +369,8 @@ extern "C" zp_status zp_sync_status(zp_ctx *ctx, void *stream) {
 }
 
 extern "C" zp_status zp_validate_batch(zp_ctx *ctx, const zp_pool *p, const zp_batch *b) {
-    zp::Args a; Path path; int NW, RB;
-    zp_status rc = prepare(ctx, "zp_validate_batch", p, b, true, &a, &path, &NW, &RB);
+    zp::Args a; Path path; zp::MfmaGeo geo;
+    zp_status rc = prepare(ctx, "zp_validate_batch", p, b, true, &a, &path, &geo);
     if (rc) return rc;
     const int B = b->B, nt = b->N_max - 1;
     const size_t per = (size_t)b->L * p->h_kv;

@@ -358,6 +358,27 @@ __device__ inline void compact_unit(const Args &a, const Unit &u, const int *tbl
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// acc += A B over the k values that a 16-byte piece of a row holds, 32 rows times 32 columns: lane L supplies row (column)
+// L%32 and the half L/32 of a 32-byte k step.  Register i of lane L holds entry (row 8*(i/4) + 4*(L/32) + i%4, column L%32).
+// DT 0: four fp32 values, products and sums in fp32; 1: eight bf16 values.
+template <int DT> __device__ __forceinline__ f32x16 mma32(const u32x4 &x, const u32x4 &y, f32x16 acc) {
+    if (DT) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), acc, 0, 0, 0);
+    const f32x4 xf = __builtin_bit_cast(f32x4, x), yf = __builtin_bit_cast(f32x4, y);
+#pragma unroll
+    for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xf[e], yf[e], acc, 0, 0, 0);
+    return acc;
+}
+
+// the 16-byte pieces one lane supplies of a row (see mma32); zeros past the pool's row
+template <int ROWB, bool PAD> __device__ __forceinline__ void load_row(const char *row, int hf, int row_bytes, u32x4 (&f)[ROWB / 32]) {
+#pragma unroll
+    for (int kk = 0; kk < ROWB / 32; kk++) {
+        f[kk] = u32x4{0u, 0u, 0u, 0u};
+        if (!PAD || kk * 32 + hf * 16 < row_bytes) f[kk] = *(const u32x4 *)(row + kk * 32 + hf * 16);
+    }
+}
 
 // workgroup-wide max and sum of per-thread values, same result in every thread, fixed order
 __device__ inline float block_reduce(float v, bool is_max, Misc *misc) {
@@ -440,15 +461,15 @@ __device__ inline void redundancy_valu(const Args &a, const Unit &u, const int *
     __syncthreads();
 }
 
-// The same for bf16 keys with a block size that divides 32: K_g K_g^T of 32 consecutive logical positions
+// The same on the matrix cores for a block size that divides 32: K_g K_g^T of 32 consecutive logical positions
 // (32/b whole blocks) is one 32x32 tile of the matrix cores, both operands being the same register fragments.
 // Lane L, register i holds the entry (row 8*(i/4) + 4*(L/32) + i%4, column L%32); only entries whose row and
 // column lie in the same block are used.  A wave owns a group; its 96 words of LDS hold the inverse norms and
 // the (row, value) of the entry zeroed in every column.
 // last_only: only the rows of the last block are produced (the live prefix was done from the key tiles of sweep 2).
-template <int D>
+template <int ROWB, int DT, bool PAD>
 __device__ inline void redundancy_mfma(const Args &a, const Unit &u, const int *tbl, float *rs, float *wave_scratch, bool last_only) {
-    constexpr int KK = D / 16;
+    constexpr int KK = ROWB / 32;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6, l32 = lane & 31, hf = lane >> 5;
     float *inv = wave_scratch + wv * 96, *zv = inv + 64;
     int *zr = (int *)(inv + 32);
@@ -469,14 +490,12 @@ __device__ inline void redundancy_mfma(const Args &a, const Unit &u, const int *
         if (p >= u.T || (last_only && p < stale_hi)) return -1;
         return pos_to_live(u, a, p);
     };
-    auto load_group = [&](int g, bf16x8 (&kf)[KK]) {
+    auto load_group = [&](int g, u32x4 (&kf)[KK]) {
         const int pc = live_of(g) >= 0 ? g * 32 + l32 : u.T - 1;  // rows that are not live read a valid row and are masked
         const int blk = div_b(a, pc);
-        const char *kp = a.k + row_off(a, u.ls, tbl[blk], pc - blk * a.b, u.h) + hf * 16;
-#pragma unroll
-        for (int kk = 0; kk < KK; kk++) kf[kk] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(kp + kk * 32));
+        load_row<ROWB, PAD>(a.k + row_off(a, u.ls, tbl[blk], pc - blk * a.b, u.h), hf, a.row_bytes, kf);
     };
-    bf16x8 kf[KK], kn[KK];
+    u32x4 kf[KK], kn[KK];
     int g = next_group(wv);
     if (g < ngroups) load_group(g, kf);
 #pragma unroll 1
@@ -488,7 +507,7 @@ __device__ inline void redundancy_mfma(const Args &a, const Unit &u, const int *
 #pragma unroll
         for (int i = 0; i < 16; i++) acc[i] = 0.f;
 #pragma unroll
-        for (int kk = 0; kk < KK; kk++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], kf[kk], acc, 0, 0, 0);
+        for (int kk = 0; kk < KK; kk++) acc = mma32<DT>(kf[kk], kf[kk], acc);
         float dg = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; i++) dg = i == dgi ? acc[i] : dg;
@@ -539,8 +558,6 @@ __device__ inline void redundancy_mfma(const Args &a, const Unit &u, const int *
 // registers: norms and the column rule travel by lane permutes, the row sums by adds across the 16 lanes of a row group
 // (this step sits inside the tile loop of sweep 2, where every wait on LDS holds up the whole workgroup's barrier).
 // It comes in two parts so that the caller can take the products while the key rows are in LDS and finish later.
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 // sum over the 16 lanes that share lane/16, the same bits in all of them (a + b and b + a at every step)
 __device__ __forceinline__ float row16_sum(float v) {
     auto dpp = [](float x, auto ctrl) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true)); };
@@ -601,8 +618,8 @@ __device__ __forceinline__ void block_row_sums(const Args &a, const Unit &u, con
     if (c < 4 && j_first + 4 * g + c < u.vl) rs[j_first + 4 * g + c] = mine * inv_len;
 }
 
-// D > 0: called from the matrix-core kernel for head dimension D (bf16); D = 0: generic kernel, element type DT.
-template <int D, int DT>
+// ROWB > 0: called from the matrix-core kernel for rows of up to ROWB bytes; ROWB = 0: generic kernel.  Element type DT.
+template <int ROWB, int DT, bool PAD, int NW>
 __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, const int *tbl, Misc *misc) {
     const int tid = threadIdx.x, nt = blockDim.x;
     float *S = (float *)(smem + a.off_S);
@@ -641,12 +658,12 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
         __syncthreads();
     }
     if (a.ex & EX_RED) {
-        const bool mf = D > 0 && 32 % a.b == 0;
+        const bool mf = ROWB > 0 && 32 % a.b == 0;
         if (a.ex & EX_RED_FUSED) {                               // the live prefix was done from the key tiles of sweep 2
             tmp = (float *)(smem + a.off_R);
-            if constexpr (D > 0) redundancy_mfma<D>(a, u, tbl, tmp, tmp + a.T_max, true);
+            if constexpr (ROWB > 0) redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, true);
         } else if (mf) {
-            if constexpr (D > 0) redundancy_mfma<D>(a, u, tbl, tmp, tmp + a.T_max, false);
+            if constexpr (ROWB > 0) redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, false);
         } else {
             redundancy_valu<DT>(a, u, tbl, tmp, tmp + a.T_max, (int *)(tmp + 2 * (size_t)a.T_max), tmp + 3 * (size_t)a.T_max);
         }
@@ -668,7 +685,8 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
 }
 
 // Everything after S sits in LDS: refinements, optional score output, selection, optional list output, compaction.
-template <int D, int DT>
+// REF: score refinements are compiled in (a launch without them runs a kernel that does not carry their code).
+template <int ROWB, int DT, bool PAD, bool REF, int NW>
 __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const int *tbl, const int *dst, Misc *misc) {
     const int tid = threadIdx.x, nt = blockDim.x;
     float *S = (float *)(smem + a.off_S);
@@ -678,7 +696,9 @@ __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const
         for (int t = tid; t < u.T; t += nt) S[t] = src[t];
         __syncthreads();
     }
-    if ((a.stages & STAGE_SCORE) && (a.ex & (EX_GLOBAL | EX_POOL | EX_RED))) refine_unit<D, DT>(a, u, smem, tbl, misc);
+    if constexpr (REF) {
+        if ((a.stages & STAGE_SCORE) && (a.ex & (EX_GLOBAL | EX_POOL | EX_RED))) refine_unit<ROWB, DT, PAD, NW>(a, u, smem, tbl, misc);
+    }
     if (a.scores_out) {
         float *o = a.scores_out + (size_t)u.unit * a.T_max;
         for (int t = tid; t < a.T_max; t += nt) o[t] = t < u.T ? S[t] : 0.f;
@@ -707,8 +727,8 @@ __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const
         }
     }
     if (a.stages & STAGE_COMPACT) {
-        if (a.ex & EX_MOVE_F_LDS) compact_unit<2>(a, u, tbl, dst, list, (const float *)(smem + a.off_G), u.k);
-        else if (a.ex & EX_MOVE_F) compact_unit<1>(a, u, tbl, dst, list, nullptr, u.k);
+        if (REF && (a.ex & EX_MOVE_F_LDS)) compact_unit<2>(a, u, tbl, dst, list, (const float *)(smem + a.off_G), u.k);
+        else if (REF && (a.ex & EX_MOVE_F)) compact_unit<1>(a, u, tbl, dst, list, nullptr, u.k);
         else compact_unit<0>(a, u, tbl, dst, list, nullptr, u.k);
     }
 }

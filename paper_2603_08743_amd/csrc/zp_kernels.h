@@ -61,8 +61,7 @@ struct Args {
     int off_R;                                 // LDS: [T_max] redundancy row sums + 96 words per wave for EX_RED_FUSED
     // byte offsets into dynamic LDS
     int off_S, off_tbl, off_dst, off_misc, off_union, lds_bytes;
-    // MFMA path geometry
-    int NB;                                    // 32-row query blocks in use
+    int NP;                                    // matrix-core kernel: passes over the keys (padded rows only)
 };
 
 // check-only paged decode attention (zp_check.hip)
@@ -78,15 +77,22 @@ hipError_t launch_decode_attention(const DecodeArgs &a, int items, hipStream_t s
 
 // launchers (host).  Each returns the hipError_t of the launch.
 hipError_t launch_unit_generic(const Args &a, int units, hipStream_t s);
-// returns hipErrorInvalidConfiguration when no MFMA instantiation covers (d, G, w)
-bool mfma_path_available(const Args &a, int *NW, int *RB);
-hipError_t launch_unit_mfma(const Args &a, int units, int NW, int RB, hipStream_t s);
-// instantiations by head dimension and workgroup width, one translation unit each (zp_mfma_*.hip)
-hipError_t launch_mfma_d64(const Args &a, int units, int NW, int RB, hipStream_t s);
-hipError_t launch_mfma_d64_wide(const Args &a, int units, int NW, int RB, hipStream_t s);
-hipError_t launch_mfma_d128(const Args &a, int units, int NW, int RB, hipStream_t s);
-hipError_t launch_mfma_d128_wide(const Args &a, int units, int NW, int RB, hipStream_t s);
-constexpr int KT = 64;                          // keys per LDS tile of the matrix-core kernel
-size_t mfma_union_bytes(int d, int NW, int NB);
+// Geometry of the matrix-core kernel for a launch: waves per workgroup, 32-row query blocks per wave, passes over the keys,
+// row bytes of the instantiation and whether the pool's rows are shorter than that.
+struct MfmaGeo { int NW, RB, NP, rowb; bool pad; };
+bool mfma_path_available(const Args &a, MfmaGeo *g);
+hipError_t launch_unit_mfma(const Args &a, int units, const MfmaGeo &g, hipStream_t s);
+// instantiations by row size and workgroup width, one translation unit each (zp_mfma_*.hip); _ref: with score refinements
+#define ZP_DECLARE_MFMA(name) hipError_t name(const Args &a, int units, int NW, int RB, hipStream_t s);
+ZP_DECLARE_MFMA(launch_mfma_d64) ZP_DECLARE_MFMA(launch_mfma_d64_wide) ZP_DECLARE_MFMA(launch_mfma_d64_ref) ZP_DECLARE_MFMA(launch_mfma_d64_wide_ref)
+ZP_DECLARE_MFMA(launch_mfma_d128) ZP_DECLARE_MFMA(launch_mfma_d128_wide) ZP_DECLARE_MFMA(launch_mfma_d128_ref) ZP_DECLARE_MFMA(launch_mfma_d128_wide_ref)
+#undef ZP_DECLARE_MFMA
+hipError_t launch_mfma_pad_bf16(const Args &a, int units, int rowb, int NW, hipStream_t s);
+hipError_t launch_mfma_pad_bf16_long(const Args &a, int units, int rowb, int NW, hipStream_t s);
+hipError_t launch_mfma_pad_f32(const Args &a, int units, int rowb, int NW, hipStream_t s);
+// keys per LDS tile of the matrix-core kernel: two 32-key subtiles, one for rows so long that two tiles of 64 would not
+// leave room for a second workgroup on the CU
+constexpr int mfma_tile_keys(int rowb) { return rowb <= 256 ? 64 : 32; }
+size_t mfma_union_bytes(const MfmaGeo &g);
 
 }  // namespace zp

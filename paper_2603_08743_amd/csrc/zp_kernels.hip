@@ -1,9 +1,9 @@
 // Unit kernels of libzp: one workgroup per (request, layer, kv head).
 //
-//  * unit_generic: scoring on the vector ALUs for any element type / group size / head
-//    dimension (fp32 pools, odd shapes), and the staged select-only / compact-only passes.
-//  * unit_mfma: bf16 pools.  The (G*w) x T logits are a dense contraction over d, so they run
-//    on the matrix cores (v_mfma_f32_32x32x16_bf16) from LDS-staged key tiles.
+//  * unit_mfma: the (G*w) x T logits are a dense contraction over d, so they run on the matrix cores
+//    (v_mfma_f32_32x32x16_bf16, v_mfma_f32_32x32x2_f32) from LDS-staged key tiles.
+//  * unit_generic: scoring on the vector ALUs for what does not fit there (more than 16 query heads per kv head,
+//    sequences whose scores leave no room for two key tiles in LDS), and the staged select-only / compact-only passes.
 //
 // Scores follow the appendix "Paged Attention Score": softmax over positions per window
 // query, max over the query heads of the group, mean over the window.  The max over heads
@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(256) unit_generic(const Args a) {
     Unit u;
     if (!unit_setup(a, unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map), u, tbl, dst, misc)) return;
     if (a.stages & STAGE_SCORE) score_generic<DT>(a, u, smem, tbl);
-    unit_tail<0, DT>(a, u, smem, tbl, dst, misc);
+    unit_tail<0, DT, false, true, 4>(a, u, smem, tbl, dst, misc);
 }
 
 hipError_t launch_unit_generic(const Args &a, int units, hipStream_t s) {
@@ -98,11 +98,11 @@ hipError_t launch_unit_generic(const Args &a, int units, hipStream_t s) {
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ MFMA path (bf16): geometry and dispatch
+// ------------------------------------------------------------------ matrix-core path: geometry and dispatch
 
-size_t mfma_union_bytes(int d, int NW, int NB) {
-    const size_t tile = (size_t)KT * (d * 2 + 16);
-    return 2 * tile + 2 * (size_t)NW * KT * 4 + (size_t)NB * 32 * 4;
+size_t mfma_union_bytes(const MfmaGeo &g) {
+    const int kt = mfma_tile_keys(g.rowb);
+    return 2 * (size_t)kt * (g.rowb + 16) + 2 * (size_t)g.NW * kt * 4 + (size_t)g.NW * g.RB * 32 * 4;
 }
 
 // (RB, NW) by the number of 32-row query blocks: small windows use fewer waves, large ones more rows per wave
@@ -116,20 +116,40 @@ static void pick_geometry(int NB, int *NW, int *RB) {
     else { *NW = 8; *RB = 4; }
 }
 
-bool mfma_path_available(const Args &a, int *NW, int *RB) {
-    if (a.dtype != 1 || (a.d != 128 && a.d != 64)) return false;
+// bf16 rows of 128 and 256 bytes have kernels of their own; every other row, and windows of more than 32 query blocks, runs
+// padded to the next of a few sizes.  Before, those shapes took one dot product per (query row, key) on the vector ALUs with
+// one key row per lane (uncoalesced 16-byte steps): fp32, d = 128, G = 4, w = 32, 128 units of 1040 positions 17.6 ms ->
+// 0.294 ms; bf16, d = 96, G = 3, w = 20, 72 units of up to 1248 positions 6.98 ms -> 0.154 ms.  A padded k step costs 1/16 of
+// a tile's products per 32 bytes, far less than the smallest gap between sizes would give back.
+bool mfma_path_available(const Args &a, MfmaGeo *g) {
     if (a.G < 1 || a.G > 16) return false;
     const int UL = 16 / a.G, NB = (a.w + 2 * UL - 1) / (2 * UL);
-    if (NB > 32) return false;
-    pick_geometry(NB, NW, RB);
-    return true;
+    g->NP = 1;
+    if (a.dtype == 1 && (a.d == 128 || a.d == 64) && NB <= 32) {
+        g->pad = false;
+        g->rowb = a.row_bytes;
+        pick_geometry(NB, &g->NW, &g->RB);
+        return true;
+    }
+    g->pad = true;
+    g->RB = 1;
+    g->NW = NB <= 2 ? 2 : NB <= 4 ? 4 : 8;
+    g->NP = (NB + g->NW - 1) / g->NW;
+    static const int sizes_bf16[] = {128, 192, 256, 384, 512, 1024}, sizes_f32[] = {256, 512, 1024};
+    for (int r : sizes_bf16) if (a.dtype == 1 && a.row_bytes <= r) { g->rowb = r; return true; }
+    for (int r : sizes_f32) if (a.dtype == 0 && a.row_bytes <= r) { g->rowb = r; return true; }
+    return false;
 }
 
-hipError_t launch_unit_mfma(const Args &a, int units, int NW, int RB, hipStream_t s) {
+hipError_t launch_unit_mfma(const Args &a, int units, const MfmaGeo &g, hipStream_t s) {
     if (units <= 0) return hipSuccess;
-    if (a.d == 128) return NW <= 4 ? launch_mfma_d128(a, units, NW, RB, s) : launch_mfma_d128_wide(a, units, NW, RB, s);
-    if (a.d == 64) return NW <= 4 ? launch_mfma_d64(a, units, NW, RB, s) : launch_mfma_d64_wide(a, units, NW, RB, s);
-    return hipErrorInvalidConfiguration;
+    if (g.pad) {
+        if (a.dtype == 0) return launch_mfma_pad_f32(a, units, g.rowb, g.NW, s);
+        return g.rowb <= 256 ? launch_mfma_pad_bf16(a, units, g.rowb, g.NW, s) : launch_mfma_pad_bf16_long(a, units, g.rowb, g.NW, s);
+    }
+    const bool ref = (a.ex & (EX_GLOBAL | EX_POOL | EX_RED)) != 0, wide = g.NW > 4;
+    if (a.d == 128) return (ref ? (wide ? launch_mfma_d128_wide_ref : launch_mfma_d128_ref) : (wide ? launch_mfma_d128_wide : launch_mfma_d128))(a, units, g.NW, g.RB, s);
+    return (ref ? (wide ? launch_mfma_d64_wide_ref : launch_mfma_d64_ref) : (wide ? launch_mfma_d64_wide : launch_mfma_d64))(a, units, g.NW, g.RB, s);
 }
 
 }  // namespace zp

@@ -1,5 +1,5 @@
-// Matrix-core unit kernel of libzp (bf16 pools) and its launcher templates.  The instantiations are spread over
-// several translation units (zp_mfma_*.hip) so that they compile in parallel.
+// Matrix-core unit kernel of libzp and its launcher templates.  The instantiations are spread over several translation
+// units (zp_mfma_*.hip) so that they compile in parallel.
 #pragma once
 #include "zp_device.h"
 
@@ -17,9 +17,10 @@ namespace zp {
 // waves per workgroup and two workgroups per CU put four waves on every SIMD, which overlaps the matrix-core and
 // vector-ALU phases of different waves and gives the row-moving phase sixteen waves per CU to issue memory operations
 // from (measured on the 8B-like shape: 15.0 ms per launch against 17.0 ms with four waves of two blocks each).
-#define ZP_WPE(NW, RB) ((NW) == 8 && (RB) == 1 ? 4 : ((NW) >= 4 ? 2 : 1))
+// Rows above 256 bytes keep 16 more registers of query fragments per 64 bytes: half the waves.
+#define ZP_WPE(NW, RB, ROWB) ((NW) == 8 && (RB) == 1 && (ROWB) <= 256 ? 4 : ((NW) >= 4 ? 2 : 1))
 
-// ------------------------------------------------------------------ MFMA path (bf16)
+// ------------------------------------------------------------------ matrix-core path
 //
 // Query rows are laid out so that both reductions of sweep 2 stay inside a lane.  A 32x32 MFMA
 // tile gives lane L, register i the element (row 4*(L/32) + 8*(i/4) + i%4, column L%32).  With
@@ -30,25 +31,37 @@ namespace zp {
 // share every key tile through LDS.  In sweep 1 the operands swap, so a lane owns one query row
 // and 16 keys per tile and the running (max, sum) of a row never leaves its lane.
 
-template <int D> struct KTile {
-    static constexpr int ROW = D * 2 + 16;        // padded row stride in bytes: conflict-free 16-byte fragment reads
+//
+// Rows are handled as ROWB bytes of either element type (DT: 0 fp32, 1 bf16): a fragment is 16 bytes of a row, i.e. eight
+// bf16 values (one v_mfma_f32_32x32x16_bf16) or four fp32 values (four v_mfma_f32_32x32x2_f32, which multiply and add in
+// fp32), and both operands take their k index from the same bytes.  PAD: the pool's rows are shorter than ROWB; the
+// pieces beyond them are zeros in LDS and in the query fragments and add nothing.
+
+template <int ROWB> struct KTile {
+    static constexpr int KT = mfma_tile_keys(ROWB);
+    static constexpr int ROW = ROWB + 16;         // padded row stride in bytes: conflict-free 16-byte fragment reads
     static constexpr int BYTES = KT * ROW;
-    static constexpr int CPR = D * 2 / 16;        // 16-byte pieces per key row
+    static constexpr int CPR = ROWB / 16;         // 16-byte pieces per key row
 };
 
-// RED: the launch computes the lightning redundancy with block size 16 and takes the similarity tiles of the live
-// prefix from the key tiles of sweep 2 (instantiated for RB = 1 only; otherwise the keys are read a third time in the tail).
-template <int D, int RB, int NW, int GT, bool RED>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP_WPE(NW, RB)))) unit_mfma(const Args a) {
+// REF: 0 no score refinements in this launch, 1 refinements in the tail, 2 (block size 16, RB = 1, unpadded bf16 rows) the
+// lightning redundancy as well, its similarity tiles of the live prefix taken from the key tiles of sweep 2 (otherwise
+// the keys are read a third time in the tail).
+// MP: the query blocks take several passes over the keys (NP groups of NW * RB blocks), S collecting their sums.
+template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP_WPE(NW, RB, ROWB)))) unit_mfma(const Args a) {
+    constexpr bool RED = REF == 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int *tbl = (int *)(smem + a.off_tbl), *dst = (int *)(smem + a.off_dst);
     Misc *misc = (Misc *)(smem + a.off_misc);
     Unit u;
     if (!unit_setup(a, unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map), u, tbl, dst, misc)) return;
 
-    using KTl = KTile<D>;
-    constexpr int NT = NW * 64, KK = D / 16, LPT = KT * KTl::CPR / NT;
-    static_assert(KT * KTl::CPR % NT == 0, "tile pieces must divide evenly among the threads");
+    using KTl = KTile<ROWB>;
+    constexpr int KT = KTl::KT, CPR = KTl::CPR, NT = NW * 64, KK = ROWB / 32;
+    constexpr bool EVEN = NT % CPR == 0 && KT * CPR % NT == 0;   // a thread fetches the same piece of every row it takes
+    constexpr int LPT = (KT * CPR + NT - 1) / NT;
+    static_assert(NT >= KT && (PAD || EVEN), "unpadded rows divide evenly among the threads");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hf = lane >> 5;
     const int G = GT ? GT : a.G, UL = 16 / G, w = a.w;
     float *S = (float *)(smem + a.off_S);
@@ -57,24 +70,28 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     float *lse = part + 2 * NW * KT;                         // [NB*32] per padded query row
     const float c = a.scale_log2;
 
-    for (int t = tid; t < u.T; t += NT) S[t] = 0.f;          // stale positions stay 0
+    const int row_bytes = PAD ? a.row_bytes : ROWB;
 
-    // query fragments: this lane supplies padded row l32 of each of its blocks, 8 elements per 16-wide k step
-    bf16x8 qf[RB][KK];
+    for (int t = tid; t < u.T; t += NT) S[t] = 0.f;          // stale positions stay 0
+    const int np = MP ? a.NP : 1;
+#pragma unroll 1
+    for (int pass = 0; pass < np; pass++) {
+    // query fragments: this lane supplies padded row l32 of each of its blocks, 16 bytes per k step
+    u32x4 qf[RB][KK];
     int u_col[RB];                                           // window row this lane owns in sweep 1 (-1: zero row)
 #pragma unroll
     for (int rb = 0; rb < RB; rb++) {
-        const int gb = wv * RB + rb;
+        const int gb = (pass * NW + wv) * RB + rb;
         const int mh = (l32 >> 2) & 1, i = ((l32 >> 3) << 2) | (l32 & 3);
         const int ul = i / G, g = i - ul * G, uu = (gb * 2 + mh) * UL + ul;
         const bool ok = ul < UL && uu < w;
         u_col[rb] = ok ? uu : -1;
-        const char *qp = a.q + ((((size_t)u.ls * a.M + u.slot) * w + (ok ? uu : 0)) * a.h_q + u.h * G + g) * (size_t)(D * 2) + hf * 16;
+        const char *qp = a.q + ((((size_t)u.ls * a.M + u.slot) * w + (ok ? uu : 0)) * a.h_q + u.h * G + g) * (size_t)row_bytes + hf * 16;
 #pragma unroll
         for (int kk = 0; kk < KK; kk++) {
             u32x4 raw = {0u, 0u, 0u, 0u};
-            if (ok) raw = *(const u32x4 *)(qp + kk * 32);
-            qf[rb][kk] = __builtin_bit_cast(bf16x8, raw);
+            if (ok && (!PAD || kk * 32 + hf * 16 < row_bytes)) raw = *(const u32x4 *)(qp + kk * 32);
+            qf[rb][kk] = raw;
         }
     }
 
@@ -84,16 +101,17 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     u32x4 stA[LPT], stB[LPT];
     // a thread always fetches the same 16-byte piece of rows r0, r0 + RSTEP, ...: one 64-bit base, then
     // base + token * (bytes between consecutive tokens) with token = block * b + slot (fits 32 bits, host-checked)
-    constexpr int RSTEP = NT / KTl::CPR;
-    const int r0 = tid / KTl::CPR;
-    const char *kbase = a.k + ((size_t)u.ls * a.N_total * a.b * a.h_kv + u.h) * (size_t)(D * 2) + (tid - r0 * KTl::CPR) * 16;
-    const unsigned tok_bytes = (unsigned)a.h_kv * (D * 2);
+    constexpr int RSTEP = NT / CPR;
+    const int r0 = tid / CPR;
+    const int piece0 = (tid - r0 * CPR) * 16;
+    const char *kbase = a.k + ((size_t)u.ls * a.N_total * a.b * a.h_kv + u.h) * (size_t)row_bytes + (EVEN ? piece0 : 0);
+    const unsigned tok_bytes = (unsigned)a.h_kv * row_bytes;
     const int gap = (u.N - 1) * a.b - u.vl;                   // stale positions between the live prefix and the last block
     auto gload = [&](int tile, u32x4 (&st)[LPT], auto nt_tag) {   // rows past the end repeat the last key (masked later)
         // Tiles that lie wholly in the live prefix (all but the last one or two) need none of the edge handling when
         // the block size is a power of two: position = live index.  (Eight-wave workgroups only: with fewer waves a
         // thread loads eight or sixteen pieces per tile and the second copy of that code costs registers.)
-        if (NW == 8 && a.b_shift >= 0 && (tile + 1) * KT <= u.vl) {
+        if (NW == 8 && EVEN && !PAD && a.b_shift >= 0 && (tile + 1) * KT <= u.vl) {
 #pragma unroll
             for (int i = 0; i < LPT; i++) {
                 const int j = tile * KT + i * RSTEP + r0;
@@ -105,7 +123,12 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         }
 #pragma unroll
         for (int i = 0; i < LPT; i++) {
-            int j = tile * KT + r0 + i * RSTEP;
+            const int pc = tid + i * NT, row = EVEN ? r0 + i * RSTEP : pc / CPR, off = EVEN ? piece0 : (pc - row * CPR) * 16;
+            if (PAD) {                                        // pieces past the pool's row, and past the tile, are zeros
+                st[i] = u32x4{0u, 0u, 0u, 0u};
+                if (off >= row_bytes || (!EVEN && row >= KT)) continue;
+            }
+            int j = tile * KT + row;
             j = j < u.Tv ? j : u.Tv - 1;
             const int t = j < u.vl ? j : j + gap;
             unsigned tok;
@@ -116,14 +139,21 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
                 const int blk = t / a.b;
                 tok = (unsigned)tbl[blk] * (unsigned)a.b + (unsigned)(t - blk * a.b);
             }
-            if (decltype(nt_tag)::value) st[i] = __builtin_nontemporal_load((const u32x4 *)(kbase + (size_t)tok * tok_bytes));
-            else st[i] = *(const u32x4 *)(kbase + (size_t)tok * tok_bytes);
+            const char *kp = kbase + (size_t)tok * tok_bytes + (EVEN ? 0 : off);
+            if (decltype(nt_tag)::value) st[i] = __builtin_nontemporal_load((const u32x4 *)kp);
+            else st[i] = *(const u32x4 *)kp;
         }
     };
-    const int lds_st = r0 * KTl::ROW + (tid - r0 * KTl::CPR) * 16;
+    const int lds_st = r0 * KTl::ROW + piece0;
     auto lstore = [&](char *buf, const u32x4 (&st)[LPT]) {
 #pragma unroll
-        for (int i = 0; i < LPT; i++) *(u32x4 *)(buf + lds_st + i * RSTEP * KTl::ROW) = st[i];
+        for (int i = 0; i < LPT; i++) {
+            if (EVEN) *(u32x4 *)(buf + lds_st + i * RSTEP * KTl::ROW) = st[i];
+            else {
+                const int pc = tid + i * NT, row = pc / CPR;
+                if (row < KT) *(u32x4 *)(buf + row * KTl::ROW + (pc - row * CPR) * 16) = st[i];
+            }
+        }
     };
     char *buf0 = kbuf, *buf1 = kbuf + KTl::BYTES;
     f32x16 zero16;
@@ -141,14 +171,14 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         constexpr bool edge = decltype(edge_tag)::value;
 #pragma unroll
         for (int sub = 0; sub < KT / 32; sub++) {
+            if (PAD && edge && j0 + sub * 32 >= u.Tv) break;  // nothing left of the sequence (unpadded: costs the eight-wave redundancy kernel 13 spills)
             f32x16 acc[RB];
             const char *kp = buf + (sub * 32 + l32) * KTl::ROW + hf * 16;
 #pragma unroll
             for (int kk = 0; kk < KK; kk++) {
-                const bf16x8 kf = *(const bf16x8 *)(kp + kk * 32);
+                const u32x4 kf = *(const u32x4 *)(kp + kk * 32);
 #pragma unroll
-                for (int rb = 0; rb < RB; rb++)
-                    acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[rb][kk], kk ? acc[rb] : zero16, 0, 0, 0);
+                for (int rb = 0; rb < RB; rb++) acc[rb] = mma32<DT>(kf, qf[rb][kk], kk ? acc[rb] : zero16);
             }
             // acc[rb][i]: key j0 + sub*32 + 4*hf + 8*(i/4) + i%4, query row = this lane's column
 #pragma unroll
@@ -220,7 +250,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
 #pragma unroll
     for (int rb = 0; rb < RB; rb++) {
         const int gb = wv * RB + rb;
-        ub[rb] = (gb * 2 + hf) * UL;
+        ub[rb] = ((pass * NW * RB + gb) * 2 + hf) * UL;
 #pragma unroll
         for (int i = 0; i < 16; i++) lrn[rb][i] = -lse[gb * 32 + 4 * hf + 8 * (i >> 2) + (i & 3)] * inv_c;
     }
@@ -230,14 +260,14 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         constexpr bool edge = decltype(edge_tag)::value;
 #pragma unroll
         for (int sub = 0; sub < KT / 32; sub++) {
+            if (PAD && edge && j0 + sub * 32 >= u.Tv) break;  // nothing left of the sequence (unpadded: costs the eight-wave redundancy kernel 13 spills)
             f32x16 acc[RB];
             const char *kp = buf + (sub * 32 + l32) * KTl::ROW + hf * 16;
 #pragma unroll
             for (int kk = 0; kk < KK; kk++) {
-                const bf16x8 kf = *(const bf16x8 *)(kp + kk * 32);
+                const u32x4 kf = *(const u32x4 *)(kp + kk * 32);
 #pragma unroll
-                for (int rb = 0; rb < RB; rb++)
-                    acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[rb][kk], kf, kk ? acc[rb] : lrn[rb], 0, 0, 0);
+                for (int rb = 0; rb < RB; rb++) acc[rb] = mma32<DT>(qf[rb][kk], kf, kk ? acc[rb] : lrn[rb]);
             }
             // acc[rb][i]: slot i of this half-wave, key j = j0 + sub*32 + l32
             const int j = j0 + sub * 32 + l32;
@@ -284,7 +314,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
 #pragma unroll
         for (int h = 0; h < HOLD; h++) {
             const int q = wv + h * NW;
-            if (q < PER && j0 + 16 * q < u.vl) gacc[h] = block_gram<D, KTl::ROW>(buf + 16 * q * KTl::ROW, lane);
+            if (q < PER && j0 + 16 * q < u.vl) gacc[h] = block_gram<ROWB / 2, KTl::ROW>(buf + 16 * q * KTl::ROW, lane);
         }
     };
     // jA: live index of the first tile (products held in gacc); bufB / jB: the second tile, jB < 0 if there is none
@@ -298,7 +328,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             for (int q = wv; q < 2 * PER; q += NW) {
                 const int qq = q - PER;
                 if (qq >= 0 && jB + 16 * qq < u.vl)
-                    block_row_sums(a, u, block_gram<D, KTl::ROW>(bufB + 16 * qq * KTl::ROW, lane), jB + 16 * qq, inv_len, rs_red, lane);
+                    block_row_sums(a, u, block_gram<ROWB / 2, KTl::ROW>(bufB + 16 * qq * KTl::ROW, lane), jB + 16 * qq, inv_len, rs_red, lane);
             }
         }
     };
@@ -313,7 +343,12 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
                 float s = 0.f;
 #pragma unroll
                 for (int v = 0; v < NW; v++) s += pt[v * KT + tid];
-                S[live_to_pos(u, a, jj)] = s / (float)w;
+                const int t = live_to_pos(u, a, jj);
+                if (MP) {
+                    s += S[t];
+                    if (pass + 1 < np) { S[t] = s; return; }
+                }
+                S[t] = s / (float)w;
             }
         }
     };
@@ -345,51 +380,63 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         reduce_tile(pt1, (rt - 1) * KT);
     }
     __syncthreads();
-    unit_tail<D, 1>(a, u, smem, tbl, dst, misc);
+    }
+    unit_tail<ROWB, DT, PAD, REF != 0, NW>(a, u, smem, tbl, dst, misc);
 }
 
-template <int D, int RB, int NW>
-static hipError_t launch_g(const Args &a, int units, hipStream_t s) {
-    const dim3 grid(units), block(NW * 64);
-#define ZP_LAUNCH(GT)                                                                                  \
-    {                                                                                                  \
-        if constexpr (RB == 1) {                                                                       \
-            if (a.ex & EX_RED_FUSED) {                                                                 \
-                hipError_t e = allow_big_lds(unit_mfma<D, RB, NW, GT, true>);                          \
-                if (e != hipSuccess) return e;                                                         \
-                hipLaunchKernelGGL((unit_mfma<D, RB, NW, GT, true>), grid, block, a.lds_bytes, s, a);  \
-                break;                                                                                 \
-            }                                                                                          \
-        }                                                                                              \
-        hipError_t e = allow_big_lds(unit_mfma<D, RB, NW, GT, false>);                                 \
-        if (e != hipSuccess) return e;                                                                 \
-        hipLaunchKernelGGL((unit_mfma<D, RB, NW, GT, false>), grid, block, a.lds_bytes, s, a);         \
-    }                                                                                                  \
-    break;
-    switch (a.G) {
-        case 4: ZP_LAUNCH(4)
-        case 5: ZP_LAUNCH(5)
-        case 7: ZP_LAUNCH(7)
-        case 8: ZP_LAUNCH(8)
-        default: ZP_LAUNCH(0)
-    }
-#undef ZP_LAUNCH
+template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP>
+static hipError_t launch_one(const Args &a, int units, hipStream_t s) {
+    hipError_t e = allow_big_lds(unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP>);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP>), dim3(units), dim3(NW * 64), a.lds_bytes, s, a);
     return hipGetLastError();
 }
 
-// the (RB, NW) geometries of one head dimension: WIDE = 0 up to four waves, WIDE = 1 eight waves
-template <int D, int WIDE>
+// ALL_REF: the refinement variants of a geometry (REF 1, and 2 where it exists); otherwise the plain one
+template <int ROWB, int RB, int NW, int GT, bool ALL_REF>
+static hipError_t launch_ref(const Args &a, int units, hipStream_t s) {
+    if constexpr (!ALL_REF) return launch_one<1, ROWB, false, RB, NW, GT, 0, false>(a, units, s);
+    else {
+        if constexpr (RB == 1) if (a.ex & EX_RED_FUSED) return launch_one<1, ROWB, false, RB, NW, GT, 2, false>(a, units, s);
+        return launch_one<1, ROWB, false, RB, NW, GT, 1, false>(a, units, s);
+    }
+}
+
+template <int ROWB, int RB, int NW, bool ALL_REF>
+static hipError_t launch_g(const Args &a, int units, hipStream_t s) {
+    switch (a.G) {
+        case 4: return launch_ref<ROWB, RB, NW, 4, ALL_REF>(a, units, s);
+        case 5: return launch_ref<ROWB, RB, NW, 5, ALL_REF>(a, units, s);
+        case 7: return launch_ref<ROWB, RB, NW, 7, ALL_REF>(a, units, s);
+        case 8: return launch_ref<ROWB, RB, NW, 8, ALL_REF>(a, units, s);
+        default: return launch_ref<ROWB, RB, NW, 0, ALL_REF>(a, units, s);
+    }
+}
+
+// the (RB, NW) geometries of unpadded bf16 rows of one size: WIDE = 0 up to four waves, WIDE = 1 eight waves
+template <int ROWB, int WIDE, bool ALL_REF>
 static hipError_t launch_d(const Args &a, int units, int NW, int RB, hipStream_t s) {
     if constexpr (!WIDE) {
-        if (RB == 1 && NW == 1) return launch_g<D, 1, 1>(a, units, s);
-        if (RB == 1 && NW == 2) return launch_g<D, 1, 2>(a, units, s);
-        if (RB == 1 && NW == 4) return launch_g<D, 1, 4>(a, units, s);
+        if (RB == 1 && NW == 1) return launch_g<ROWB, 1, 1, ALL_REF>(a, units, s);
+        if (RB == 1 && NW == 2) return launch_g<ROWB, 1, 2, ALL_REF>(a, units, s);
+        if (RB == 1 && NW == 4) return launch_g<ROWB, 1, 4, ALL_REF>(a, units, s);
     } else {
-        if (RB == 1 && NW == 8) return launch_g<D, 1, 8>(a, units, s);
-        if (RB == 2 && NW == 8) return launch_g<D, 2, 8>(a, units, s);
-        if (RB == 3 && NW == 8) return launch_g<D, 3, 8>(a, units, s);
-        if (RB == 4 && NW == 8) return launch_g<D, 4, 8>(a, units, s);
+        if (RB == 1 && NW == 8) return launch_g<ROWB, 1, 8, ALL_REF>(a, units, s);
+        if (RB == 2 && NW == 8) return launch_g<ROWB, 2, 8, ALL_REF>(a, units, s);
+        if (RB == 3 && NW == 8) return launch_g<ROWB, 3, 8, ALL_REF>(a, units, s);
+        if (RB == 4 && NW == 8) return launch_g<ROWB, 4, 8, ALL_REF>(a, units, s);
     }
+    return hipErrorInvalidConfiguration;
+}
+
+// every other row: padded to the next size that is instantiated, one query block per wave, up to eight waves, as many
+// passes as the window needs, group size at run time
+template <int DT, int ROWB>
+static hipError_t launch_pad(const Args &a, int units, int NW, hipStream_t s) {
+    const bool ref = (a.ex & (EX_GLOBAL | EX_POOL | EX_RED)) != 0;
+    if (NW == 2) return ref ? launch_one<DT, ROWB, true, 1, 2, 0, 1, false>(a, units, s) : launch_one<DT, ROWB, true, 1, 2, 0, 0, false>(a, units, s);
+    if (NW == 4) return ref ? launch_one<DT, ROWB, true, 1, 4, 0, 1, false>(a, units, s) : launch_one<DT, ROWB, true, 1, 4, 0, 0, false>(a, units, s);
+    if (NW == 8) return ref ? launch_one<DT, ROWB, true, 1, 8, 0, 1, true>(a, units, s) : launch_one<DT, ROWB, true, 1, 8, 0, 0, true>(a, units, s);
     return hipErrorInvalidConfiguration;
 }
 

@@ -1,6 +1,6 @@
-// Instantiations of the matrix-core unit kernel for head dimension 64, eight waves per workgroup.
+// Instantiations of the matrix-core unit kernel for bf16 rows of 128 bytes (head dimension 64), eight waves per workgroup.
 #include "zp_mfma.h"
 
 namespace zp {
-hipError_t launch_mfma_d64_wide(const Args &a, int units, int NW, int RB, hipStream_t s) { return launch_d<64, 1>(a, units, NW, RB, s); }
+hipError_t launch_mfma_d64_wide(const Args &a, int units, int NW, int RB, hipStream_t s) { return launch_d<128, 1, false>(a, units, NW, RB, s); }
 }  // namespace zp
