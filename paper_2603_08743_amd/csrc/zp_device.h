@@ -550,6 +550,172 @@ __device__ inline void redundancy_mfma(const Args &a, const Unit &u, const int *
     __syncthreads();
 }
 
+// Any other block size on the matrix cores.  The similarity matrix of one block is cut into 32-column groups; a wave owns a
+// group and goes through the block's 32-row groups, own rows first, each one 32x32 tile (lane L holds column L%32, 16 of the
+// rows).  A column's sum and the last row above p stay in its two lanes over all tiles; the matrix is symmetric, so the sum of
+// column r is the sum of row r before zeroing, and what was zeroed in row r is taken off in a pass of its own (waves go
+// through the columns that have a zeroed entry only).  inv, zr, zv: LDS, by logical position: inverse norm (0: not live),
+// row zeroed in the column (-1: none) and its value.
+// Row fragments come from L2 (the unit's keys have just been swept), with few waves (PF) those of the next tile requested
+// before the current tile is worked on.  Before, one thread per key took b dot products one element at a time: 345 ms per launch for 1152 units
+// of 2304 positions in blocks of 256 (d 128, bf16), now 1.71 ms.
+template <int ROWB, int DT, bool PAD, bool PF>
+__device__ inline void redundancy_blocks(const Args &a, const Unit &u, const int *tbl, float *rs, float *inv, int *zr, float *zv) {
+    constexpr int KK = ROWB / 32;
+    constexpr bool HOLD = ROWB <= 256;                           // fragments of three row sets fit the registers
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6, l32 = lane & 31, hf = lane >> 5;
+    const int b = a.b, stale_hi = (u.N - 1) * b;
+    const float inv_len = 1.0f / (float)u.Tv;
+    auto row_ptr = [&](int p) {                                  // p: a logical position of the request
+        const int blk = div_b(a, p);
+        return a.k + row_off(a, u.ls, tbl[blk], p - blk * b, u.h);
+    };
+    f32x16 zero16;
+#pragma unroll
+    for (int i = 0; i < 16; i++) zero16[i] = 0.f;
+    auto gram_stream = [&](const char *rp, const char *cp) {     // long rows: both operands a few pieces at a time
+        f32x16 acc = zero16;
+#pragma unroll 4
+        for (int kk = 0; kk < KK; kk++) {
+            u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u};
+            if (!PAD || kk * 32 + hf * 16 < a.row_bytes) {
+                x = *(const u32x4 *)(rp + kk * 32 + hf * 16);
+                y = *(const u32x4 *)(cp + kk * 32 + hf * 16);
+            }
+            acc = mma32<DT>(x, y, acc);
+        }
+        return acc;
+    };
+    // inverse norms from the diagonals of 32x32 tiles of consecutive positions
+    const int dgi = ((l32 >> 3) << 2) | (l32 & 3);
+    const bool dg_mine = hf == ((l32 >> 2) & 1);
+    for (int g = wv; g * 32 < u.T; g += nw) {
+        const int p = g * 32 + l32;
+        const bool live = p < u.T && pos_to_live(u, a, p) >= 0;
+        if (g * 32 < u.vl || g * 32 + 32 > stale_hi) {
+            const char *rp = row_ptr(live ? p : u.T - 1);
+            f32x16 acc = zero16;
+            if constexpr (HOLD) {
+                u32x4 f[KK];
+                load_row<ROWB, PAD>(rp, hf, a.row_bytes, f);
+#pragma unroll
+                for (int kk = 0; kk < KK; kk++) acc = mma32<DT>(f[kk], f[kk], acc);
+            } else acc = gram_stream(rp, rp);
+            float dg = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; i++) dg = i == dgi ? acc[i] : dg;
+            if (dg_mine && p < u.T) inv[p] = (live && dg > 0.f) ? 1.0f / sqrtf(dg) : 0.f;
+        } else if (hf == 0) inv[p] = 0.f;
+    }
+    __syncthreads();
+
+    const int ncg = (b + 31) >> 5, items = u.N * ncg;
+    auto wanted = [&](int it) {                                  // next column group of this wave that has a live key
+        for (; it < items; it += nw) {
+            const int blk = it / ncg, p0 = blk * b + (it - blk * ncg) * 32;
+            if (p0 < u.vl || blk == u.N - 1) break;
+        }
+        return it;
+    };
+    auto load_group = [&](int it, int step, u32x4 (&f)[HOLD ? KK : 1]) {   // rows of the group `step` places after the item's own
+        const int blk = it / ncg, cg = it - blk * ncg, rg = cg + step < ncg ? cg + step : cg + step - ncg;
+        const int r = rg * 32 + l32;
+        const char *rp = row_ptr(blk * b + (r < b ? r : b - 1));
+        if constexpr (HOLD) load_row<ROWB, PAD>(rp, hf, a.row_bytes, f);
+        return rp;
+    };
+    u32x4 cur[HOLD ? KK : 1], nxt[HOLD ? KK : 1], col[HOLD ? KK : 1];
+    int it = wanted(wv);
+    const char *cp = nullptr, *rp = nullptr, *rpn = nullptr;
+    if (it < items) rp = load_group(it, 0, cur);
+#pragma unroll 1
+    while (it < items) {
+        const int itn = wanted(it + nw);
+        const int blk = it / ncg, cg = it - blk * ncg, c = cg * 32 + l32;
+        const float *binv = inv + blk * b;
+        const float ic = c < b ? binv[c] : 0.f;
+        float csum = 0.f, lastv = 0.f;
+        int last = -1;
+        cp = rp;
+        if constexpr (HOLD) {
+#pragma unroll
+            for (int kk = 0; kk < KK; kk++) col[kk] = cur[kk];
+        }
+#pragma unroll 1
+        for (int step = 0; step < ncg; step++) {
+            if (PF) {
+                if (step + 1 < ncg) rpn = load_group(it, step + 1, nxt);
+                else if (itn < items) rpn = load_group(itn, 0, nxt);
+            }
+            f32x16 acc = zero16;
+            if constexpr (HOLD) {
+#pragma unroll
+                for (int kk = 0; kk < KK; kk++) acc = mma32<DT>(cur[kk], col[kk], acc);
+            } else acc = gram_stream(rp, cp);
+            const int rg = cg + step < ncg ? cg + step : cg + step - ncg;
+            const int r0 = rg * 32 + 4 * hf;                     // register i: row r0 + 8*(i/4) + i%4
+            float mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                const int r = r0 + 8 * (i >> 2) + (i & 3);
+                const float ir = r < b ? binv[r] : 0.f;
+                const float v = (ir != 0.f && ic != 0.f && r != c) ? acc[i] * (ir * ic) : 0.f;
+                acc[i] = v;
+                csum += v;
+                mx = fmaxf(mx, v);
+            }
+            if (__any(mx > a.p_thr)) {
+#pragma unroll
+                for (int i = 0; i < 16; i++) {
+                    const int r = r0 + 8 * (i >> 2) + (i & 3);
+                    if (acc[i] > a.p_thr && r > last && r < b) { last = r; lastv = acc[i]; }
+                }
+            }
+            if (PF) {
+                rp = rpn;
+                if constexpr (HOLD) {
+#pragma unroll
+                    for (int kk = 0; kk < KK; kk++) cur[kk] = nxt[kk];
+                }
+            } else if (step + 1 < ncg) rp = load_group(it, step + 1, cur);
+            else if (itn < items) rp = load_group(itn, 0, cur);
+        }
+        const int o_last = __shfl_xor(last, 32);
+        const float o_lastv = __shfl_xor(lastv, 32), o_csum = __shfl_xor(csum, 32);
+        if (hf == 0 && c < b) {
+            const int p = blk * b + c, j = pos_to_live(u, a, p);
+            if (o_last > last) { last = o_last; lastv = o_lastv; }
+            zr[p] = j >= 0 ? last : -1;
+            zv[p] = lastv;
+            if (j >= 0) rs[j] = csum + o_csum;
+        }
+        it = itn;
+    }
+    __syncthreads();
+
+    for (int w0 = wv; w0 < u.N * ((b + 63) >> 6); w0 += nw) {     // 64 rows of one block per wave
+        const int nr = (b + 63) >> 6, blk = w0 / nr, r = (w0 - blk * nr) * 64 + lane;
+        const int j = r < b ? pos_to_live(u, a, blk * b + r) : -1;
+        if (!__any(j >= 0)) continue;
+        float corr = 0.f;
+        for (int c0 = 0; c0 < b; c0 += 64) {
+            int row = -1;
+            float val = 0.f;
+            // column groups without a live key were not visited
+            if (c0 + lane < b && pos_to_live(u, a, blk * b + c0 + lane) >= 0) { row = zr[blk * b + c0 + lane]; val = zv[blk * b + c0 + lane]; }
+            unsigned long long m = __ballot(row >= 0);
+            while (m) {                                          // columns ascend
+                const int l = __builtin_ctzll(m);
+                m &= m - 1;
+                const float v = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, val), l));
+                corr += __builtin_amdgcn_readlane(row, l) == r ? v : 0.f;
+            }
+        }
+        if (j >= 0) rs[j] = (rs[j] - corr) * inv_len;
+    }
+    __syncthreads();
+}
+
 // Block size 16, live prefix: the similarity matrix of one block from the key tile that sweep 2 holds in LDS anyway
 // (rows `rows`, ROWB bytes apart, 16 keys of one block).  K_blk K_blk^T is one 16x16 tile of the matrix cores
 // (v_mfma_f32_16x16x32_bf16, both operands the same fragments: lane L supplies key L%16, elements 8*(L/16).. of every
@@ -619,7 +785,8 @@ __device__ __forceinline__ void block_row_sums(const Args &a, const Unit &u, con
 }
 
 // ROWB > 0: called from the matrix-core kernel for rows of up to ROWB bytes; ROWB = 0: generic kernel.  Element type DT.
-template <int ROWB, int DT, bool PAD, int NW>
+// REF 2: a launch whose similarity tiles came from sweep 2 (EX_RED_FUSED), REF 1: any other with refinements.
+template <int ROWB, int DT, bool PAD, int REF, int NW>
 __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, const int *tbl, Misc *misc) {
     const int tid = threadIdx.x, nt = blockDim.x;
     float *S = (float *)(smem + a.off_S);
@@ -658,14 +825,16 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
         __syncthreads();
     }
     if (a.ex & EX_RED) {
-        const bool mf = ROWB > 0 && 32 % a.b == 0;
-        if (a.ex & EX_RED_FUSED) {                               // the live prefix was done from the key tiles of sweep 2
+        if constexpr (REF == 2) {                                // the live prefix was done from the key tiles of sweep 2
             tmp = (float *)(smem + a.off_R);
-            if constexpr (ROWB > 0) redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, true);
-        } else if (mf) {
+            redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, true);
+        } else if (ROWB > 0 && 32 % a.b == 0) {
             if constexpr (ROWB > 0) redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, false);
         } else {
-            redundancy_valu<DT>(a, u, tbl, tmp, tmp + a.T_max, (int *)(tmp + 2 * (size_t)a.T_max), tmp + 3 * (size_t)a.T_max);
+            float *inv = tmp + a.T_max, *zv = tmp + 3 * (size_t)a.T_max;
+            int *zr = (int *)(tmp + 2 * (size_t)a.T_max);
+            if constexpr (ROWB > 0) redundancy_blocks<ROWB, DT, PAD, NW <= 4>(a, u, tbl, tmp, inv, zr, zv);
+            else redundancy_valu<DT>(a, u, tbl, tmp, inv, zr, zv);
         }
         // R = softmax over the live sequence of (row sum / Tv) / tau, in base 2
         float m = -INFINITY;
@@ -686,7 +855,7 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
 
 // Everything after S sits in LDS: refinements, optional score output, selection, optional list output, compaction.
 // REF: score refinements are compiled in (a launch without them runs a kernel that does not carry their code).
-template <int ROWB, int DT, bool PAD, bool REF, int NW>
+template <int ROWB, int DT, bool PAD, int REF, int NW>
 __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const int *tbl, const int *dst, Misc *misc) {
     const int tid = threadIdx.x, nt = blockDim.x;
     float *S = (float *)(smem + a.off_S);
@@ -696,8 +865,8 @@ __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const
         for (int t = tid; t < u.T; t += nt) S[t] = src[t];
         __syncthreads();
     }
-    if constexpr (REF) {
-        if ((a.stages & STAGE_SCORE) && (a.ex & (EX_GLOBAL | EX_POOL | EX_RED))) refine_unit<ROWB, DT, PAD, NW>(a, u, smem, tbl, misc);
+    if constexpr (REF != 0) {
+        if ((a.stages & STAGE_SCORE) && (a.ex & (EX_GLOBAL | EX_POOL | EX_RED))) refine_unit<ROWB, DT, PAD, REF, NW>(a, u, smem, tbl, misc);
     }
     if (a.scores_out) {
         float *o = a.scores_out + (size_t)u.unit * a.T_max;
@@ -727,8 +896,8 @@ __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const
         }
     }
     if (a.stages & STAGE_COMPACT) {
-        if (REF && (a.ex & EX_MOVE_F_LDS)) compact_unit<2>(a, u, tbl, dst, list, (const float *)(smem + a.off_G), u.k);
-        else if (REF && (a.ex & EX_MOVE_F)) compact_unit<1>(a, u, tbl, dst, list, nullptr, u.k);
+        if (REF != 0 && (a.ex & EX_MOVE_F_LDS)) compact_unit<2>(a, u, tbl, dst, list, (const float *)(smem + a.off_G), u.k);
+        else if (REF != 0 && (a.ex & EX_MOVE_F)) compact_unit<1>(a, u, tbl, dst, list, nullptr, u.k);
         else compact_unit<0>(a, u, tbl, dst, list, nullptr, u.k);
     }
 }

@@ -381,7 +381,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     }
     __syncthreads();
     }
-    unit_tail<ROWB, DT, PAD, REF != 0, NW>(a, u, smem, tbl, dst, misc);
+    unit_tail<ROWB, DT, PAD, REF, NW>(a, u, smem, tbl, dst, misc);
 }
 
 template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP>
