@@ -13,6 +13,9 @@
 #include <unordered_set>
 #include <vector>
 
+#define ZP_SLOTS 4
+static const size_t kSlotBytes = 24u << 20;
+
 struct zp_ctx {
     int device;
     int *d_status;   // 8 words on the device: flag, unit, reason
@@ -20,6 +23,12 @@ struct zp_ctx {
     int xcd_map;     // workgroup -> unit map: 1 contiguous ranges per XCD, 0 identity
     int n_cu;        // compute units: every kernel here fits at least one workgroup per CU
     char err[512];
+    // Workspaces of the calls that take several launches (partial sums of sweep 1, scores between the launches).  A call takes the
+    // one its stream used last, else the next in turn, waits on the device for that one's last call and records an event after
+    // its own: calls on different streams stay apart, and one that has to share is merely ordered behind the other.
+    struct Slot { char *mem; hipEvent_t done; void *stream; bool used; } slot[ZP_SLOTS];
+    int next_slot;
+    std::mutex slot_mu;
 };
 
 static thread_local char g_err[512] = "";
@@ -57,6 +66,15 @@ extern "C" zp_status zp_create(zp_ctx **out) {
         delete c;
         return rc;
     }
+    // without workspaces (no memory left for them) every call takes one launch
+    char *mem = nullptr;
+    bool ok = hipMalloc((void **)&mem, ZP_SLOTS * kSlotBytes) == hipSuccess;
+    for (auto &w : c->slot) ok = ok && hipEventCreateWithFlags(&w.done, hipEventDisableTiming) == hipSuccess;
+    if (ok) for (int i = 0; i < ZP_SLOTS; i++) c->slot[i].mem = mem + i * kSlotBytes;
+    else {
+        if (mem) (void)hipFree(mem);
+        (void)hipGetLastError();                              // nobody's error
+    }
     *out = c;
     return ZP_OK;
 }
@@ -65,6 +83,8 @@ extern "C" void zp_destroy(zp_ctx *ctx) {
     if (!ctx) return;
     (void)hipFree(ctx->d_status);
     (void)hipHostFree(ctx->h_status);
+    if (ctx->slot[0].mem) (void)hipFree(ctx->slot[0].mem);
+    for (auto &w : ctx->slot) if (w.done) (void)hipEventDestroy(w.done);
     delete ctx;
 }
 
@@ -185,8 +205,89 @@ extern "C" size_t zp_scratch_bytes(const zp_pool *pool, const zp_batch *batch) {
     return 0;
 }
 
+// With one workgroup per unit, a launch of fewer units than compute units leaves the rest idle, and one unit's two sweeps,
+// selection and row moving follow each other on its own.  Up to three quarters of the compute units such calls take three
+// launches instead: sweep 1 and sweep 2 with up to eight workgroups per unit (a run of its key tiles each), then selection and
+// row moving with the rows cut into slices.  Measured (256 compute units): 64 units of 4112 positions (d 128, G 4, w 64)
+// 266 -> 120 us; 72 units of up to 1248 (d 96, w 20) 154 -> 75 us; 128 fp32 units of 1040 295 -> 200 us; staged, 192 units of up
+// to 4128 310 -> 228 us.  At 256 units of 4112 the one launch is the better one (351 us against 408 us: its phases overlap
+// between workgroups), at 448 of 2064 more so (276 against 403 us), and below 512 positions three launches cost more than they
+// share out (16 positions: 14 us against 28 us).
+static bool few_units(const zp_ctx *ctx, long long units) { return units <= ctx->n_cu * 3 / 4; }
+
+// Workgroups per unit of the two scoring launches (0: one launch does everything).  Four instead of eight: 125, 79, 190 and 234 us.
+static int split_parts(const zp_ctx *ctx, const zp::Args &a, Path path, const zp::MfmaGeo &geo, hipStream_t s) {
+    const long long units = (long long)a.B * a.L_slab * a.h_kv;
+    if (path != PATH_MFMA || geo.NP != 1 || a.ex || !ctx->slot[0].mem || units <= 0 || a.T_max < 512 || !few_units(ctx, units)) return 0;
+    const long long seg = units * ZP_SEGMENTS * geo.NW * geo.RB * 32 * (long long)sizeof(float2);
+    if (seg + units * a.T_max * 4 > (long long)kSlotBytes) return 0;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();                               // not the launch's error
+        return 0;
+    }
+    return cap == hipStreamCaptureStatusNone ? ZP_SEGMENTS : 0;   // a graph may run beside anything: no shared workspace
+}
+
+// Row-moving workgroups per unit: K and V apart, rows cut into 128-byte (64-byte) pieces while that makes no more than two
+// workgroups per compute unit.  64 units that move 4096 rows of 256 bytes in K and V: 64 us with the selection, 3.9 TB/s.
+static void pick_slices(const zp_ctx *ctx, zp::Args *a, int units) {
+    a->slices = 2;
+    a->slice_bytes = a->row_bytes;
+    for (int piece = 128; piece >= 64; piece >>= 1)
+        if (a->row_bytes % piece == 0 && a->row_bytes > piece && (long long)units * 2 * (a->row_bytes / piece) <= 2 * ctx->n_cu) {
+            a->slices = 2 * (a->row_bytes / piece);
+            a->slice_bytes = piece;
+            break;
+        }
+}
+
+static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, const zp::MfmaGeo &geo, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(ctx->slot_mu);
+    int i = -1;
+    for (int j = 0; j < ZP_SLOTS; j++) if (ctx->slot[j].used && ctx->slot[j].stream == (void *)s) i = j;
+    if (i < 0) { i = ctx->next_slot; ctx->next_slot = (i + 1) % ZP_SLOTS; }
+    zp_ctx::Slot &w = ctx->slot[i];
+    hipError_t e = w.used ? hipStreamWaitEvent(s, w.done, 0) : hipSuccess;
+    if (e != hipSuccess) return e;
+    const bool whole = (a.stages & zp::STAGE_SELECT) != 0;
+    const size_t seg_bytes = (size_t)units * ZP_SEGMENTS * geo.NW * geo.RB * 32 * sizeof(float2);
+    float *scores = whole ? (float *)(w.mem + seg_bytes) : a.scores_out;
+    zp::Args m = a;                                           // scoring
+    m.stages = zp::STAGE_SCORE;
+    m.keep_idx_out = nullptr;
+    m.seg = (float2 *)w.mem;
+    m.scores_out = scores;
+    m.parts = parts;
+    w.used = true;
+    w.stream = (void *)s;
+    for (m.phase = 1; m.phase <= 2 && e == hipSuccess; m.phase++) e = zp::launch_unit_mfma(m, units, geo, s);
+    if (e == hipSuccess && whole) {                           // selection and row moving
+        a.stages = zp::STAGE_LOAD_SCORES | zp::STAGE_SELECT | zp::STAGE_COMPACT | zp::STAGE_CHECK_SLOT;
+        a.scores_in = scores;
+        a.scores_in_stride = a.T_max;
+        a.lds_bytes = a.off_union + align16(a.budget * 4);
+        pick_slices(ctx, &a, units);
+        e = zp::launch_unit_sliced(a, units, s);
+    }
+    const hipError_t er = hipEventRecord(w.done, s);
+    return e != hipSuccess ? e : er;
+}
+
 static zp_status launch(zp_ctx *ctx, const char *who, zp::Args &a, Path path, const zp::MfmaGeo &geo, void *stream) {
     const int units = a.B * a.L_slab * a.h_kv;
+    if (const int parts = split_parts(ctx, a, path, geo, (hipStream_t)stream)) {
+        const hipError_t e = launch_split(ctx, a, parts, units, geo, (hipStream_t)stream);
+        if (e != hipSuccess) return fail(ctx, ZP_EHIP, "%s: kernel launch failed: %s", who, hipGetErrorString(e));
+        return ZP_OK;
+    }
+    if (path == PATH_GENERIC && !a.ex && !(a.stages & zp::STAGE_SCORE) && few_units(ctx, units)) {   // staged select or compact
+        if (a.stages & zp::STAGE_COMPACT) pick_slices(ctx, &a, units);
+        else a.slices = 1;
+        const hipError_t e = zp::launch_unit_sliced(a, units, (hipStream_t)stream);
+        if (e != hipSuccess) return fail(ctx, ZP_EHIP, "%s: kernel launch failed: %s", who, hipGetErrorString(e));
+        return ZP_OK;
+    }
     hipError_t e = path == PATH_MFMA ? zp::launch_unit_mfma(a, units, geo, (hipStream_t)stream)
                                      : zp::launch_unit_generic(a, units, (hipStream_t)stream);
     if (e != hipSuccess) return fail(ctx, ZP_EHIP, "%s: kernel launch failed: %s", who, hipGetErrorString(e));
@@ -313,6 +414,8 @@ extern "C" zp_status zp_compress_static(const zp_pool *pool, const zp_batch *bat
     }
     zp_ctx tmp;                                               // host-side only: carries defaults and the error text
     tmp.device = dev; tmp.d_status = words; tmp.h_status = nullptr; tmp.xcd_map = 1; tmp.n_cu = 0; tmp.err[0] = 0;
+    for (auto &w : tmp.slot) w = {};
+    tmp.next_slot = 0;
     zp::Args a; Path path; zp::MfmaGeo geo;
     zp_status rc = prepare(&tmp, "zp_compress_static", pool, batch, true, &a, &path, &geo);
     if (rc == ZP_OK && !len_out && batch->B > 0) rc = fail(&tmp, ZP_EINVAL, "zp_compress_static: len_out is NULL");

@@ -107,7 +107,7 @@ __device__ inline int unit_scalars(const Args &a, int unit, Unit &u) {
         const int cap = a.budget < u.Tv ? a.budget : u.Tv;
         if (u.k < a.w || u.k > cap) return BAD_KEEP;
     }
-    if (a.stages & STAGE_SCORE) {
+    if (a.stages & (STAGE_SCORE | STAGE_CHECK_SLOT)) {
         u.slot = a.q_slot[u.n];
         if (u.slot < 0 || u.slot >= a.M) return BAD_SLOT;
     }
@@ -349,6 +349,48 @@ __device__ inline void compact_unit(const Args &a, const Unit &u, const int *tbl
     if (a.b_shift < 0) compact_rows<FM, false, false>(a, u, tbl, dst, list, Sg, k);
     else if (blockDim.x <= 128) compact_rows<FM, true, true>(a, u, tbl, dst, list, Sg, k);
     else compact_rows<FM, true, false>(a, u, tbl, dst, list, Sg, k);
+}
+
+// Compaction by several workgroups per unit: each moves `slice_bytes` of every row of one pool.  Slices never touch each
+// other's bytes, so every workgroup is alias-safe by the argument above, in place as well.
+template <int U, bool POW2>
+__device__ __forceinline__ void compact_slice(const Args &a, const Unit &u, const int *tbl, const int *dst, const int *list, int k, int slice) {
+    const int tid = threadIdx.x;
+    const int cpr = a.slice_bytes >> 4, rpp = blockDim.x / cpr, rsub = tid / cpr;
+    const bool active = rsub < rpp;
+    char *pool = (slice & 1) ? a.v : a.k;
+    const size_t base = ((size_t)u.ls * a.N_total * a.b * a.h_kv + u.h) * (size_t)a.row_bytes + (size_t)(slice >> 1) * a.slice_bytes + ((tid - rsub * cpr) << 4);
+    const unsigned tok_bytes = (unsigned)a.h_kv * (unsigned)a.row_bytes;
+#pragma unroll 1
+    for (int r0 = 0; r0 < k; r0 += U * rpp) {
+        u32x4 x[U];
+        unsigned dt[U];
+        bool mv[U];
+#pragma unroll
+        for (int i = 0; i < U; i++) {
+            const int r = r0 + i * rpp + rsub;
+            mv[i] = false;
+            if (active && r < k) {
+                const int t = list[r];
+                unsigned st;
+                if (POW2) {
+                    st = ((unsigned)tbl[t >> a.b_shift] << a.b_shift) + (unsigned)(t & (a.b - 1));
+                    dt[i] = ((unsigned)dst[r >> a.b_shift] << a.b_shift) + (unsigned)(r & (a.b - 1));
+                } else {
+                    const int sb = t / a.b, db = r / a.b;
+                    st = (unsigned)tbl[sb] * (unsigned)a.b + (unsigned)(t - sb * a.b);
+                    dt[i] = (unsigned)dst[db] * (unsigned)a.b + (unsigned)(r - db * a.b);
+                }
+                mv[i] = st != dt[i];
+                if (mv[i]) x[i] = ZP_NT_LOAD((const u32x4 *)(pool + base + (size_t)st * tok_bytes));
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < U; i++)
+            if (mv[i]) ZP_NT_STORE(x[i], (u32x4 *)(pool + base + (size_t)dt[i] * tok_bytes));
+    }
 }
 
 // ------------------------------------------------------------------ score refinements
@@ -855,8 +897,9 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
 
 // Everything after S sits in LDS: refinements, optional score output, selection, optional list output, compaction.
 // REF: score refinements are compiled in (a launch without them runs a kernel that does not carry their code).
-template <int ROWB, int DT, bool PAD, int REF, int NW>
-__device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const int *tbl, const int *dst, Misc *misc) {
+// SLICED: this workgroup is one of a.slices that move the unit's rows; the first of them writes the other outputs.
+template <int ROWB, int DT, bool PAD, int REF, int NW, bool SLICED = false>
+__device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const int *tbl, const int *dst, Misc *misc, int slice = 0) {
     const int tid = threadIdx.x, nt = blockDim.x;
     float *S = (float *)(smem + a.off_S);
     int *list = (int *)(smem + a.off_union);
@@ -868,18 +911,18 @@ __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const
     if constexpr (REF != 0) {
         if ((a.stages & STAGE_SCORE) && (a.ex & (EX_GLOBAL | EX_POOL | EX_RED))) refine_unit<ROWB, DT, PAD, REF, NW>(a, u, smem, tbl, misc);
     }
-    if (a.scores_out) {
+    if (a.scores_out && (!SLICED || slice == 0)) {
         float *o = a.scores_out + (size_t)u.unit * a.T_max;
         for (int t = tid; t < a.T_max; t += nt) o[t] = t < u.T ? S[t] : 0.f;
         __syncthreads();
     }
     if (a.stages & STAGE_SELECT) {
         select_unit(a, u, (unsigned *)S, list, misc);
-        if (a.keep_idx_out) {
+        if (a.keep_idx_out && (!SLICED || slice == 0)) {
             int *o = a.keep_idx_out + (size_t)u.unit * a.budget;
             for (int r = tid; r < a.budget; r += nt) o[r] = r < u.k ? list[r] : -1;
         }
-        if (a.len_out && tid == 0) a.len_out[u.unit] = u.k;
+        if (a.len_out && tid == 0 && (!SLICED || slice == 0)) a.len_out[u.unit] = u.k;
     }
     if (a.stages & STAGE_LOAD_LIST) {
         const int *src = a.keep_idx_in + (size_t)u.unit * a.budget;
@@ -896,6 +939,11 @@ __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const
         }
     }
     if (a.stages & STAGE_COMPACT) {
+        if constexpr (SLICED) {
+            if (a.b_shift >= 0) compact_slice<8, true>(a, u, tbl, dst, list, u.k, slice);
+            else compact_slice<8, false>(a, u, tbl, dst, list, u.k, slice);
+            return;
+        }
         if (REF != 0 && (a.ex & EX_MOVE_F_LDS)) compact_unit<2>(a, u, tbl, dst, list, (const float *)(smem + a.off_G), u.k);
         else if (REF != 0 && (a.ex & EX_MOVE_F)) compact_unit<1>(a, u, tbl, dst, list, nullptr, u.k);
         else compact_unit<0>(a, u, tbl, dst, list, nullptr, u.k);

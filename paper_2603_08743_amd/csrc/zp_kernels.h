@@ -12,6 +12,7 @@ enum : int {
     STAGE_COMPACT = 4,  // move kept K/V rows
     STAGE_LOAD_SCORES = 8,  // S comes from args.scores_in instead of STAGE_SCORE
     STAGE_LOAD_LIST = 16,   // the kept list comes from args.keep_idx_in / len_in
+    STAGE_CHECK_SLOT = 32,  // a launch after the scoring launches of the same call: units they skipped are skipped here too
 };
 
 // Score refinements switched on for a launch (appendix "Global Score", "Pooling at the Sequence Dimension",
@@ -62,6 +63,11 @@ struct Args {
     // byte offsets into dynamic LDS
     int off_S, off_tbl, off_dst, off_misc, off_union, lds_bytes;
     int NP;                                    // matrix-core kernel: passes over the keys (padded rows only)
+    // few units: several workgroups per unit, one launch per dependency (the rule and its figures: split_parts in zp_api.hip)
+    int phase;                                 // matrix-core kernel: 0 whole unit, 1 sweep 1 of a part, 2 sweep 2 of a part
+    int parts;                                 // workgroups per unit (phases 1 and 2)
+    float2 *seg;                               // [units][ZP_SEGMENTS][query rows, padded]: (reference, sum) of sweep 1 per segment
+    int slices, slice_bytes;                   // row-moving kernel: workgroups per unit, bytes of a row each of them moves
 };
 
 // check-only paged decode attention (zp_check.hip)
@@ -77,6 +83,11 @@ hipError_t launch_decode_attention(const DecodeArgs &a, int items, hipStream_t s
 
 // launchers (host).  Each returns the hipError_t of the launch.
 hipError_t launch_unit_generic(const Args &a, int units, hipStream_t s);
+hipError_t launch_unit_sliced(const Args &a, int units, hipStream_t s);
+// The keys of a unit are cut into at most ZP_SEGMENTS runs of whole tiles, a function of their number alone.  Sweep 1 sums
+// every run by itself and the runs are put together in ascending order, whichever workgroups they ran in: a call gives the
+// same bits with one workgroup per unit and with several.
+#define ZP_SEGMENTS 8
 // Geometry of the matrix-core kernel for a launch: waves per workgroup, 32-row query blocks per wave, passes over the keys,
 // row bytes of the instantiation and whether the pool's rows are shorter than that.
 struct MfmaGeo { int NW, RB, NP, rowb; bool pad; };

@@ -98,6 +98,26 @@ hipError_t launch_unit_generic(const Args &a, int units, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Selection and row moving with several workgroups per unit, for launches of few units: every workgroup selects for itself
+// (nothing to hand over, and the units would leave the other compute units idle) and moves its slice of the rows.
+__global__ void __launch_bounds__(1024) unit_sliced(const Args a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    int *tbl = (int *)(smem + a.off_tbl), *dst = (int *)(smem + a.off_dst);
+    Misc *misc = (Misc *)(smem + a.off_misc);
+    const int v = unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map);
+    Unit u;
+    if (!unit_setup(a, v / a.slices, u, tbl, dst, misc)) return;
+    unit_tail<0, 1, false, 0, 16, true>(a, u, smem, tbl, dst, misc, v % a.slices);
+}
+
+hipError_t launch_unit_sliced(const Args &a, int units, hipStream_t s) {
+    if (units <= 0) return hipSuccess;
+    hipError_t e = allow_big_lds(unit_sliced);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(unit_sliced, dim3(units * a.slices), dim3(1024), a.lds_bytes, s, a);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ matrix-core path: geometry and dispatch
 
 size_t mfma_union_bytes(const MfmaGeo &g) {

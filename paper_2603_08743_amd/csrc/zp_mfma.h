@@ -37,6 +37,12 @@ namespace zp {
 // fp32), and both operands take their k index from the same bytes.  PAD: the pool's rows are shorter than ROWB; the
 // pieces beyond them are zeros in LDS and in the query fragments and add nothing.
 
+// tiles of a segment: an even number (two tiles are worked on per turn of the loops), at least four
+__device__ __forceinline__ int segment_tiles(int ntiles) {
+    const int s = 2 * ((ntiles + 2 * ZP_SEGMENTS - 1) / (2 * ZP_SEGMENTS));
+    return s < 4 ? 4 : s;
+}
+
 template <int ROWB> struct KTile {
     static constexpr int KT = mfma_tile_keys(ROWB);
     static constexpr int ROW = ROWB + 16;         // padded row stride in bytes: conflict-free 16-byte fragment reads
@@ -48,14 +54,16 @@ template <int ROWB> struct KTile {
 // lightning redundancy as well, its similarity tiles of the live prefix taken from the key tiles of sweep 2 (otherwise
 // the keys are read a third time in the tail).
 // MP: the query blocks take several passes over the keys (NP groups of NW * RB blocks), S collecting their sums.
-template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP>
+template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP, int PH = 0>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP_WPE(NW, RB, ROWB)))) unit_mfma(const Args a) {
     constexpr bool RED = REF == 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int *tbl = (int *)(smem + a.off_tbl), *dst = (int *)(smem + a.off_dst);
     Misc *misc = (Misc *)(smem + a.off_misc);
     Unit u;
-    if (!unit_setup(a, unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map), u, tbl, dst, misc)) return;
+    int uid = unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map), part_no = 0;
+    if (PH) { part_no = uid % a.parts; uid /= a.parts; }
+    if (!unit_setup(a, uid, u, tbl, dst, misc)) return;
 
     using KTl = KTile<ROWB>;
     constexpr int KT = KTl::KT, CPR = KTl::CPR, NT = NW * 64, KK = ROWB / 32;
@@ -96,6 +104,17 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     }
 
     const int ntiles = (u.Tv + KT - 1) / KT;
+    // this workgroup's tiles [t_lo, t_hi)
+    const int seg_len = segment_tiles(ntiles);
+    int t_lo = 0, t_hi = ntiles;
+    if (PH) {
+        const int per = ZP_SEGMENTS / a.parts * seg_len;
+        t_lo = part_no * per;
+        t_hi = t_lo + per < ntiles ? t_lo + per : ntiles;
+        if (t_lo >= ntiles) return;
+    }
+    const int n_here = t_hi - t_lo;
+    float2 *seg = a.seg + (size_t)u.unit * ZP_SEGMENTS * (NW * RB * 32);
     // Key tiles travel HBM -> registers -> LDS.  Two register sets alternate so that a tile is requested two
     // iterations before it is needed (one tile of compute is shorter than the HBM latency).
     u32x4 stA[LPT], stB[LPT];
@@ -215,28 +234,78 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         if (j0 + KT > u.Tv - w) sweep1_body(buf, j0, std::true_type());
         else sweep1_body(buf, j0, std::false_type());
     };
-    gload(0, stA, ZP_NT1());
+    // end of a segment: the two half-waves hold the same row, different keys; then the segments in ascending order
+    float *lsum = part;                                      // [NB*32] sums beside the references in lse (part: sweep 2 only)
+    auto merge = [](float &m, float &l, float m2, float l2) {
+        const float mm = fmaxf(m, m2);
+        l = fmaf(l, fexp2(m - mm), l2 * fexp2(m2 - mm));
+        m = mm;
+    };
+    auto close_segment = [&](int sg) {
+        asm volatile("" ::: "memory");                       // keeps the addresses below out of the tile loop: 12 spilled registers with REF 2, 26 without
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) {
+            const float mo = __shfl_xor(rm[rb], 32), lo = __shfl_xor(rl[rb], 32);
+            const int row = (wv * RB + rb) * 32 + l32;
+            if (hf == 0) {
+                merge(rm[rb], rl[rb], mo, lo);
+                if (PH) seg[sg * (NW * RB * 32) + row] = make_float2(rm[rb], rl[rb]);
+                else {
+                    float m = rm[rb], l = rl[rb];
+                    if (sg) {
+                        m = lse[row], l = lsum[row];
+                        merge(m, l, rm[rb], rl[rb]);
+                    }
+                    lse[row] = m;
+                    lsum[row] = l;
+                }
+            }
+            rm[rb] = -1e30f;
+            rl[rb] = 0.f;
+        }
+    };
+    if constexpr (PH != 2) {
+    gload(t_lo, stA, ZP_NT1());
     lstore(buf0, stA);
-    if (ntiles > 1) gload(1, stA, ZP_NT1());
+    if (n_here > 1) gload(t_lo + 1, stA, ZP_NT1());
     __syncthreads();
+    int sg = PH ? t_lo / seg_len : 0, seg_end = t_lo + seg_len;                            // segments have an even number of tiles, the last one aside
 #pragma unroll 1
-    for (int it = 0; it < ntiles; it += 2) {
-        if (it + 2 < ntiles) gload(it + 2, stB, ZP_NT1());
+    for (int it = t_lo; it < t_hi; it += 2) {
+        if (it + 2 < t_hi) gload(it + 2, stB, ZP_NT1());
         sweep1_tile(buf0, it * KT);
-        if (it + 1 < ntiles) lstore(buf1, stA);
+        if (it + 1 < t_hi) lstore(buf1, stA);
         __syncthreads();
-        if (it + 1 >= ntiles) break;
-        if (it + 3 < ntiles) gload(it + 3, stA, ZP_NT1());
+        if (it + 1 >= t_hi) break;
+        if (it + 3 < t_hi) gload(it + 3, stA, ZP_NT1());
         sweep1_tile(buf1, (it + 1) * KT);
-        if (it + 2 < ntiles) lstore(buf0, stB);
+        if (it + 2 < t_hi) lstore(buf0, stB);
+        if (it + 2 == seg_end && seg_end < t_hi) {
+            close_segment(sg++);
+            seg_end += seg_len;
+        }
         __syncthreads();
     }
+    close_segment(sg);
+    if (PH == 1) return;
+    }
+    if (hf == 0) {
 #pragma unroll
-    for (int rb = 0; rb < RB; rb++) {                         // the two half-waves hold the same row, different keys
-        const float mo = __shfl_xor(rm[rb], 32), lo = __shfl_xor(rl[rb], 32);
-        const float mm = fmaxf(rm[rb], mo);
-        const float ll = rl[rb] * fexp2(rm[rb] - mm) + lo * fexp2(mo - mm);
-        if (hf == 0) lse[(wv * RB + rb) * 32 + l32] = u_col[rb] >= 0 ? mm + flog2(ll) : INFINITY;
+        for (int rb = 0; rb < RB; rb++) {
+            const int row = (wv * RB + rb) * 32 + l32;
+            float m, l;
+            if (PH) {
+                const float2 s0 = seg[row];
+                m = s0.x, l = s0.y;
+                for (int sg = 1; sg * seg_len < ntiles; sg++) {
+                    const float2 s = seg[sg * (NW * RB * 32) + row];
+                    merge(m, l, s.x, s.y);
+                }
+            } else {
+                m = lse[row], l = lsum[row];
+            }
+            lse[row] = u_col[rb] >= 0 ? m + flog2(l) : INFINITY;
+        }
     }
     __syncthreads();
 
@@ -353,42 +422,59 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         }
     };
     float *pt0 = part, *pt1 = part + NW * KT;
-    // tiles are taken in DESCENDING order (tile number rt = ntiles-1-it): the keys sweep 1 read last are the ones
+    // tiles are taken in DESCENDING order (tile number rt = t_hi-1-it): the keys sweep 1 read last are the ones
     // most likely to be still in L2 / Infinity Cache
-    gload(ntiles - 1, stA, ZP_NT2());
+    gload(t_hi - 1, stA, ZP_NT2());
     lstore(buf0, stA);
-    if (ntiles > 1) gload(ntiles - 2, stA, ZP_NT2());
+    if (n_here > 1) gload(t_hi - 2, stA, ZP_NT2());
     __syncthreads();
 #pragma unroll 1
-    for (int it = 0; it < ntiles; it += 2) {
-        const int rt = ntiles - 1 - it;
-        if (it + 2 < ntiles) gload(rt - 2, stB, ZP_NT2());
+    for (int it = 0; it < n_here; it += 2) {
+        const int rt = t_hi - 1 - it;
+        if (it + 2 < n_here) gload(rt - 2, stB, ZP_NT2());
         sweep2_tile(buf0, pt0, rt * KT);
         if (RED) {
             gram_first(buf0, rt * KT);
-            if (it + 1 >= ntiles) gram_finish(rt * KT, nullptr, -1);
+            if (it + 1 >= n_here) gram_finish(rt * KT, nullptr, -1);
         }
-        if (it + 1 < ntiles) lstore(buf1, stA);
+        if (it + 1 < n_here) lstore(buf1, stA);
         __syncthreads();
         reduce_tile(pt0, rt * KT);
-        if (it + 1 >= ntiles) break;
-        if (it + 3 < ntiles) gload(rt - 3, stA, ZP_NT2());
+        if (it + 1 >= n_here) break;
+        if (it + 3 < n_here) gload(rt - 3, stA, ZP_NT2());
         sweep2_tile(buf1, pt1, (rt - 1) * KT);
         if (RED) gram_finish(rt * KT, buf1, (rt - 1) * KT);
-        if (it + 2 < ntiles) lstore(buf0, stB);
+        if (it + 2 < n_here) lstore(buf0, stB);
         __syncthreads();
         reduce_tile(pt1, (rt - 1) * KT);
     }
     __syncthreads();
+    if (PH) {                                                // (one pass) this part's scores; the first part clears what is not live
+        float *o = a.scores_out + (size_t)u.unit * a.T_max;
+        const int j1 = t_hi * KT < u.Tv ? t_hi * KT : u.Tv;
+        for (int j = t_lo * KT + tid; j < j1; j += NT) {
+            const int t = live_to_pos(u, a, j);
+            o[t] = S[t];
+        }
+        if (part_no == 0) {
+            for (int t = u.vl + tid; t < (u.N - 1) * a.b; t += NT) o[t] = 0.f;
+            for (int t = u.T + tid; t < a.T_max; t += NT) o[t] = 0.f;
+        }
+        return;
+    }
     }
     unit_tail<ROWB, DT, PAD, REF, NW>(a, u, smem, tbl, dst, misc);
 }
 
-template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP>
+template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP, int PH = 0>
 static hipError_t launch_one(const Args &a, int units, hipStream_t s) {
-    hipError_t e = allow_big_lds(unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP>);
+    if constexpr (REF == 0 && PH == 0) {
+        if (a.phase == 1) return launch_one<DT, ROWB, PAD, RB, NW, GT, REF, MP, 1>(a, units, s);
+        if (a.phase == 2) return launch_one<DT, ROWB, PAD, RB, NW, GT, REF, MP, 2>(a, units, s);
+    }
+    hipError_t e = allow_big_lds(unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP, PH>);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP>), dim3(units), dim3(NW * 64), a.lds_bytes, s, a);
+    hipLaunchKernelGGL((unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP, PH>), dim3(PH ? units * a.parts : units), dim3(NW * 64), a.lds_bytes, s, a);
     return hipGetLastError();
 }
 

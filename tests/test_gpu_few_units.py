@@ -1,0 +1,95 @@
+"""Calls of few units, which take three launches with several workgroups per unit: around the segment and tile edges of the split,
+every wave geometry, stale gaps and shared workspaces; bit for bit what one launch gives."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_08743_amd import binding
+from tests import gpu_util as G
+from tests.util import random_problem
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(seed, bf16, d, Gq, w, b, N_max, extra=1, gaps=True, B=2, L=1):
+    p = random_problem(seed, B=B, L=L, h_kv=2, G=Gq, d=d, b=b, N_max=N_max, w=w, extra_blocks=extra, bf16=bf16, heavy=4)
+    rng = np.random.default_rng(seed)
+    N, budget = N_max + extra, (N_max - 1) * b
+    vl = np.full((B, L, 2), (N - 1) * b, dtype=np.int32)
+    if gaps:
+        vl = rng.integers(max(w - b, 0), (N - 1) * b + 1, size=vl.shape).astype(np.int32)
+        vl[0, 0, 0] = (N - 1) * b
+        vl[-1, 0, 1] = max(w - b, 0)                              # a single segment, whatever the others have
+    cap = np.minimum(budget, vl + b)
+    p.valid_len, p.keep = vl, (w + (rng.random(vl.shape) * (cap - w + 1)).astype(np.int32)).clip(w, cap).astype(np.int32)
+    return p
+
+
+def captured_scores(pool, batch):
+    """The same call in a graph: one launch does the scoring."""
+    ref, _, _ = G.alloc_outputs(pool, batch)
+    G.ctx().zp_score(pool, batch, ref)                            # loads the kernel outside the capture
+    torch.cuda.synchronize()
+    ref.fill_(float("nan"))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        G.ctx().zp_score(pool, batch, ref)
+    graph.replay()
+    torch.cuda.synchronize()
+    return ref
+
+
+@pytest.mark.parametrize("bf16,d,Gq,w,b,N_max", [
+    (True, 128, 4, 64, 16, 31), (True, 128, 4, 64, 16, 127), (True, 128, 4, 64, 16, 128), (True, 128, 4, 8, 16, 63),  # 512 positions; whole and ragged segments
+    (True, 128, 2, 16, 16, 40), (True, 128, 7, 32, 24, 30), (True, 128, 5, 128, 16, 66), (True, 128, 8, 128, 32, 20),  # 1, 8, 22 and 32 query blocks
+    (True, 64, 4, 33, 16, 64), (True, 64, 5, 17, 8, 65),
+    (True, 96, 3, 20, 24, 42), (True, 192, 4, 16, 16, 34), (False, 128, 4, 32, 16, 64), (False, 64, 1, 3, 16, 33), (False, 256, 2, 9, 12, 45),
+])
+def test_split_gives_the_bits_of_one_launch(bf16, d, Gq, w, b, N_max):
+    p = problem(300 + d + w, bf16, d, Gq, w, b, N_max)
+    pool, batch = G.to_device(p)
+    scores, _, _ = G.alloc_outputs(pool, batch)
+    G.ctx().zp_score(pool, batch, scores)
+    assert torch.equal(scores.view(torch.int32), captured_scores(pool, batch).view(torch.int32))
+    rep = G.full_protocol(p, pool, batch)
+    assert rep["worst_rel"] < 1e-3
+
+
+def test_more_streams_than_workspaces():
+    c = G.ctx()
+    jobs = []
+    for i in range(6):
+        pool, batch = G.to_device(problem(900 + i, True, 128, 4, 32, 16, 60 + i))
+        expect = G.clone_pool(pool)
+        elen = torch.empty((2, 1, 2), dtype=torch.int32, device="cuda")
+        c.zp_compress(expect, batch, elen)
+        jobs.append((pool, batch, torch.cuda.Stream(), torch.full_like(elen, -7), expect, elen))
+    torch.cuda.synchronize()
+    for pool, batch, stream, ln, _, _ in jobs:
+        with torch.cuda.stream(stream):
+            c.zp_compress(pool, batch, ln)
+    torch.cuda.synchronize()
+    for pool, _, _, ln, expect, elen in jobs:
+        assert torch.equal(ln, elen)
+        assert torch.equal(pool.k.view(torch.int16), expect.k.view(torch.int16)) and torch.equal(pool.v.view(torch.int16), expect.v.view(torch.int16))
+
+
+@pytest.mark.parametrize("what", ["slot", "block", "keep"])
+def test_bad_unit_is_skipped_by_every_launch(what):
+    p = problem(77, True, 128, 4, 32, 16, 40, gaps=False)
+    pool, batch = G.to_device(p)
+    before = G.clone_pool(pool)
+    if what == "slot":
+        batch.q_slot[0] = pool.q.shape[1]
+    elif what == "block":
+        batch.block_table[0, 3] = pool.k.shape[1]
+    else:
+        batch.keep[0] = 1
+    ln = torch.full((2, 1, 2), -7, dtype=torch.int32, device="cuda")
+    G.ctx().zp_compress(pool, batch, ln)
+    with pytest.raises(binding.ZpError):
+        G.ctx().zp_sync_status()
+    assert (ln[0] == -1).all() and torch.equal(ln[1], batch.keep[1])
+    own = torch.from_numpy(p.block_table[0].astype(np.int64)).cuda()
+    assert torch.equal(pool.k[:, own].view(torch.int16), before.k[:, own].view(torch.int16))
+    assert torch.equal(pool.v[:, own].view(torch.int16), before.v[:, own].view(torch.int16))
