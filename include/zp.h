@@ -97,8 +97,9 @@ zp_status zp_create(zp_ctx **out);
 void zp_destroy(zp_ctx *ctx);
 const char *zp_last_error(const zp_ctx *ctx); /* ctx may be NULL: text of the last failed zp_create/zp_plan */
 
-/* Device scratch zp_score / zp_compress need beyond inputs and outputs for this shape.  The kernels keep everything between
-   their steps on chip, so this is 0. */
+/* Device scratch zp_score / zp_compress need from the caller beyond inputs and outputs for this shape: none.  Calls of few
+   units use workspaces of the context (96 MB, allocated by zp_create if there is room; one per stream, calls on more than
+   four streams at once share them and are ordered behind each other on the device). */
 size_t zp_scratch_bytes(const zp_pool *pool, const zp_batch *batch);
 
 /* Tuning / test switches.  ZP_OPT_SPLIT: -1 (default) and 0 are accepted and change nothing; 1 asked for a kernel in which
@@ -150,7 +151,7 @@ zp_status zp_compress(zp_ctx *ctx, const zp_pool *pool, const zp_batch *batch, i
 
 /*
  * zp_compress for callers that cannot allocate: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Such callers cannot call zp_create (it allocates the status words the kernels report skipped
+ * forbid hipMalloc.  Such callers cannot call zp_create (it allocates workspaces and the status words the kernels report skipped
  * units through), so this call takes no context: the status words live in a device array that is part of the
  * library image, 256 bytes on every GPU the library runs on, held until the process ends.  The call allocates and
  * frees nothing, on the host or on the device, and enqueues kernels only (one small fill kernel that clears the

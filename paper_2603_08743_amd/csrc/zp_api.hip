@@ -226,7 +226,7 @@ static int split_parts(const zp_ctx *ctx, const zp::Args &a, Path path, const zp
         (void)hipGetLastError();                               // not the launch's error
         return 0;
     }
-    return cap == hipStreamCaptureStatusNone ? ZP_SEGMENTS : 0;   // a graph may run beside anything: no shared workspace
+    return cap == hipStreamCaptureStatusNone ? zp::segments_of(geo.RB) : 0;   // a graph may run beside anything: no shared workspace
 }
 
 // Row-moving workgroups per unit: K and V apart, rows cut into 128-byte (64-byte) pieces while that makes no more than two

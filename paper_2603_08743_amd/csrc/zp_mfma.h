@@ -38,8 +38,8 @@ namespace zp {
 // pieces beyond them are zeros in LDS and in the query fragments and add nothing.
 
 // tiles of a segment: an even number (two tiles are worked on per turn of the loops), at least four
-__device__ __forceinline__ int segment_tiles(int ntiles) {
-    const int s = 2 * ((ntiles + 2 * ZP_SEGMENTS - 1) / (2 * ZP_SEGMENTS));
+__device__ __forceinline__ int segment_tiles(int ntiles, int segments) {
+    const int s = 2 * ((ntiles + 2 * segments - 1) / (2 * segments));
     return s < 4 ? 4 : s;
 }
 
@@ -105,12 +105,11 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
 
     const int ntiles = (u.Tv + KT - 1) / KT;
     // this workgroup's tiles [t_lo, t_hi)
-    const int seg_len = segment_tiles(ntiles);
+    const int seg_len = segment_tiles(ntiles, segments_of(RB));
     int t_lo = 0, t_hi = ntiles;
     if (PH) {
-        const int per = ZP_SEGMENTS / a.parts * seg_len;
-        t_lo = part_no * per;
-        t_hi = t_lo + per < ntiles ? t_lo + per : ntiles;
+        t_lo = part_no * seg_len;                             // one segment each
+        t_hi = t_lo + seg_len < ntiles ? t_lo + seg_len : ntiles;
         if (t_lo >= ntiles) return;
     }
     const int n_here = t_hi - t_lo;

@@ -176,12 +176,12 @@ def cmd_resources(a):
     """Registers, spills, scratch and occupancy of every kernel instantiation, from hipcc's own remarks."""
     import re
     from .build import CSRC, FLAGS
-    files = ["zp_mfma_d128_wide.hip", "zp_mfma_d128.hip", "zp_mfma_d64_wide.hip", "zp_mfma_d64.hip", "zp_kernels.hip", "zp_check.hip"]
+    files = sorted(os.path.basename(f) for f in glob.glob(os.path.join(CSRC, "zp_mfma_*.hip"))) + ["zp_kernels.hip", "zp_check.hip"]
     rows = []
     from concurrent.futures import ThreadPoolExecutor
     compile_one = lambda f: subprocess.run(["hipcc", *FLAGS, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, f),
                                             "-o", os.devnull], capture_output=True, text=True)
-    with ThreadPoolExecutor(max_workers=len(files)) as ex:
+    with ThreadPoolExecutor(max_workers=6) as ex:
         results = list(ex.map(compile_one, files))
     for f, r in zip(files, results):
         assert r.returncode == 0, r.stderr[-2000:]
@@ -194,12 +194,14 @@ def cmd_resources(a):
     md = ["# Compiler resource usage of every kernel instantiation (gfx950)", "Command (no GPU needed):",
           "  python -m paper_2603_08743_amd.profile_summary resources",
           "  (per source file: hipcc <build flags> --cuda-device-only -Rpass-analysis=kernel-resource-usage -c csrc/<file>)", "",
-          "unit_mfma<D, RB, NW, G, RED>: head dimension, 32-row query blocks per wave, waves per workgroup, group size (0 = run time), RED = redundancy",
-          "taken from the key tiles of sweep 2.  VGPR spills go to scratch memory; SGPR spills go to spare vector-register lanes and cost no memory traffic.", "",
+          "unit_mfma<DT, ROWB, PAD, RB, NW, G, REF, MP, PH>: element type (0 fp32, 1 bf16), row bytes, padded rows, 32-row query blocks per wave, waves",
+          "per workgroup, group size (0 = run time), refinements (2: redundancy from the key tiles of sweep 2), several passes, phase (0 whole unit,",
+          "1 sweep 1, 2 sweep 2).  VGPR spills go to scratch memory; SGPR spills go to spare vector-register lanes and cost no memory traffic.", "",
           "File | kernel | VGPRs | AGPRs | VGPR spills | SGPR spills | scratch bytes/lane | waves/SIMD", "---|---|---|---|---|---|---|---"]
     md += ["%s | %s | %s | %s | %s | %s | %s | %s" % r for r in rows]
-    used = {"cfg1": "unit_mfma<128, 1, 8, 7, false>", "cfg2 / cfg3": "unit_mfma<128, 1, 8, 4, false>", "cfg2 with redundancy": "unit_mfma<128, 1, 8, 4, true>",
-            "cfg4": "unit_mfma<128, 3, 8, 5, false>", "paper geometry": "unit_mfma<128, 1, 2, 4, false>", "cfg0 (fp32)": "unit_generic<0>"}
+    unit = lambda rb, nw, g, ref: "unit_mfma<1, 256, false, %d, %d, %d, %d, false, 0>" % (rb, nw, g, ref)   # noqa: E731
+    used = {"cfg1": unit(1, 8, 7, 0), "cfg2 / cfg3": unit(1, 8, 4, 0), "cfg2 with redundancy": unit(1, 8, 4, 2), "cfg4": unit(3, 8, 5, 0),
+            "paper geometry": unit(1, 2, 4, 0), "cfg0 (fp32)": "unit_mfma<0, 256, true, 1, 2, 0, 0, false, 0>"}
     md += ["", "Instantiations the benchmark workloads run: " + "; ".join("%s: %s" % kv for kv in used.items()) + "."]
     path = os.path.join(PROFILES, "kernel_resource_usage.md")
     open(path, "w").write("\n".join(md) + "\n")
