@@ -6,6 +6,7 @@ import torch
 
 from paper_2603_08743_amd import binding
 from tests import gpu_util as G
+from tests.test_gpu_extras import pick_threshold, plant_similar_keys, run_extras_protocol
 from tests.util import random_problem
 
 pytestmark = pytest.mark.gpu
@@ -93,3 +94,14 @@ def test_bad_unit_is_skipped_by_every_launch(what):
     own = torch.from_numpy(p.block_table[0].astype(np.int64)).cuda()
     assert torch.equal(pool.k[:, own].view(torch.int16), before.k[:, own].view(torch.int16))
     assert torch.equal(pool.v[:, own].view(torch.int16), before.v[:, own].view(torch.int16))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Gq,w", [(3, 64), (4, 64), (5, 40), (7, 32), (8, 32)])
+def test_redundancy_over_all_segments(Gq, w, d):
+    """One launch with the similarity tiles from sweep 2 (eight waves) sums the same segments as the split calls it is checked against."""
+    p = random_problem(40 + Gq + d, B=1, L=1, h_kv=2, G=Gq, d=d, b=16, N_max=130, w=w, bf16=True, heavy=4)
+    plant_similar_keys(p, np.random.default_rng(Gq), 60, noise=0.1)
+    thr = pick_threshold(p, [0.4, 0.41, 0.42, 0.43] if d == 128 else [0.6, 0.61, 0.62, 0.63])
+    rep = run_extras_protocol(p, dict(alpha=0.8, pool_kernel=3, lam=0.3, tau=2e-3, p=thr), seed=Gq)
+    assert rep["worst"] < 1e-3
