@@ -141,8 +141,9 @@ zp_status zp_compact_kv(zp_ctx *ctx, const zp_pool *pool, const zp_batch *batch,
                         const int32_t *len, void *stream);
 
 /*
- * Steps (1)+(2)+(3) fused: one pass per unit, scores never leave the chip.
- * len_out: [dev] int32 [B][L_slab][h_kv].  scores_dbg / keep_idx_dbg: optional
+ * Steps (1)+(2)+(3) fused: every unit's values are read before its results are written.
+ * len_out: [dev] int32 [B][L_slab][h_kv]; it may be the batch's valid_len or keep array itself (same layout when
+ * the slab holds all layers), so that the new lengths replace the old ones in place.  scores_dbg / keep_idx_dbg: optional
  * [dev] outputs with the layouts of zp_score / zp_select_topk (NULL to skip);
  * they hold bit for bit what the staged calls produce.
  */

@@ -215,12 +215,25 @@ extern "C" size_t zp_scratch_bytes(const zp_pool *pool, const zp_batch *batch) {
 // share out (16 positions: 14 us against 28 us).
 static bool few_units(const zp_ctx *ctx, long long units) { return units <= ctx->n_cu * 3 / 4; }
 
+// Workspace of a call: partial sums of sweep 1, the units' scalars, the scores.
+static size_t seg_bytes(const zp::MfmaGeo &geo, long long units) { return (size_t)units * ZP_SEGMENTS * geo.NW * geo.RB * 32 * sizeof(float2); }
+static size_t workspace_bytes(const zp::Args &a, const zp::MfmaGeo &geo, long long units) {
+    return seg_bytes(geo, units) + (size_t)units * sizeof(int2) + (size_t)units * a.T_max * 4;
+}
+
+// len_out inside one of the arrays that every launch of a call reads again (valid_len and keep are read once, see unit_scalars)
+static bool overlaps_tables(const zp::Args &a, long long units) {
+    const uintptr_t lo = (uintptr_t)a.len_out, hi = lo + (uintptr_t)units * 4;
+    auto meets = [&](const int *p, long long n) { return a.len_out && p && lo < (uintptr_t)p + (uintptr_t)n * 4 && (uintptr_t)p < hi; };
+    return meets(a.num_blocks, a.B) || meets(a.q_slot, a.B) || meets(a.block_table, (long long)a.B * a.max_blocks) ||
+           meets(a.dst_table, (long long)a.B * (a.N_max - 1));
+}
+
 // Workgroups per unit of the two scoring launches (0: one launch does everything).  Four instead of eight: 125, 79, 190 and 234 us.
 static int split_parts(const zp_ctx *ctx, const zp::Args &a, Path path, const zp::MfmaGeo &geo, hipStream_t s) {
     const long long units = (long long)a.B * a.L_slab * a.h_kv;
     if (path != PATH_MFMA || geo.NP != 1 || a.ex || !ctx->slot[0].mem || units <= 0 || a.T_max < 512 || !few_units(ctx, units)) return 0;
-    const long long seg = units * ZP_SEGMENTS * geo.NW * geo.RB * 32 * (long long)sizeof(float2);
-    if (seg + units * a.T_max * 4 > (long long)kSlotBytes) return 0;
+    if (workspace_bytes(a, geo, units) > kSlotBytes || overlaps_tables(a, units)) return 0;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
         (void)hipGetLastError();                               // not the launch's error
@@ -251,12 +264,13 @@ static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, co
     hipError_t e = w.used ? hipStreamWaitEvent(s, w.done, 0) : hipSuccess;
     if (e != hipSuccess) return e;
     const bool whole = (a.stages & zp::STAGE_SELECT) != 0;
-    const size_t seg_bytes = (size_t)units * ZP_SEGMENTS * geo.NW * geo.RB * 32 * sizeof(float2);
-    float *scores = whole ? (float *)(w.mem + seg_bytes) : a.scores_out;
+    int2 *scalars = (int2 *)(w.mem + seg_bytes(geo, units));
+    float *scores = whole ? (float *)(scalars + units) : a.scores_out;
     zp::Args m = a;                                           // scoring
     m.stages = zp::STAGE_SCORE;
     m.keep_idx_out = nullptr;
     m.seg = (float2 *)w.mem;
+    m.unit_out = whole ? scalars : nullptr;
     m.scores_out = scores;
     m.parts = parts;
     w.used = true;
@@ -266,6 +280,7 @@ static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, co
         a.stages = zp::STAGE_LOAD_SCORES | zp::STAGE_SELECT | zp::STAGE_COMPACT | zp::STAGE_CHECK_SLOT;
         a.scores_in = scores;
         a.scores_in_stride = a.T_max;
+        a.unit_in = scalars;
         a.lds_bytes = a.off_union + align16(a.budget * 4);
         pick_slices(ctx, &a, units);
         e = zp::launch_unit_sliced(a, units, s);

@@ -93,8 +93,11 @@ __device__ inline int unit_scalars(const Args &a, int unit, Unit &u) {
     u.Tv = u.vl + a.b;
     if (u.N < a.N_max || u.N > a.max_blocks) return BAD_NUM_BLOCKS;
     const int idx = (u.n * a.L + a.layer0 + u.ls) * a.h_kv + u.h;
-    if (a.valid_len) {
-        u.vl = a.valid_len[idx];
+    // Several workgroups of a unit come through here in the launch that writes len_out, and a caller may pass valid_len or keep as
+    // len_out: the values are then those an earlier launch of the call has read.
+    const int2 fixed = a.unit_in ? a.unit_in[unit] : make_int2(0, 0);
+    if (a.unit_in || a.valid_len) {
+        u.vl = a.unit_in ? fixed.x : a.valid_len[idx];
         if (u.vl < 0 || u.vl > (u.N - 1) * a.b) return BAD_VALID_LEN;
     }
     u.Tv = u.vl + a.b;
@@ -103,7 +106,8 @@ __device__ inline int unit_scalars(const Args &a, int unit, Unit &u) {
         u.k = a.len_in[unit];
         if (u.k > a.budget) return BAD_KEEP;
     } else {
-        if (a.keep) u.k = a.keep[idx];
+        if (a.unit_in) u.k = fixed.y;
+        else if (a.keep) u.k = a.keep[idx];
         const int cap = a.budget < u.Tv ? a.budget : u.Tv;
         if (u.k < a.w || u.k > cap) return BAD_KEEP;
     }

@@ -67,6 +67,7 @@ struct Args {
     int phase;                                 // matrix-core kernel: 0 whole unit, 1 sweep 1 of a part, 2 sweep 2 of a part
     int parts;                                 // workgroups per unit (phases 1 and 2)
     float2 *seg;                               // [units][ZP_SEGMENTS][query rows, padded]: (reference, sum) of sweep 1 per segment
+    int2 *unit_out; const int2 *unit_in;       // [units]: (live prefix length, keep count) of every unit, written by phase 2, read by the launch after it
     int slices, slice_bytes;                   // row-moving kernel: workgroups per unit, bytes of a row each of them moves
 };
 

@@ -105,3 +105,17 @@ def test_redundancy_over_all_segments(Gq, w, d):
     thr = pick_threshold(p, [0.4, 0.41, 0.42, 0.43] if d == 128 else [0.6, 0.61, 0.62, 0.63])
     rep = run_extras_protocol(p, dict(alpha=0.8, pool_kernel=3, lam=0.3, tau=2e-3, p=thr), seed=Gq)
     assert rep["worst"] < 1e-3
+
+
+@pytest.mark.parametrize("into", ["valid_len", "keep"])
+def test_lengths_may_replace_valid_len_or_keep(into):
+    """128 units: more row-moving workgroups than run at once, so late ones start after the first has written its unit's length."""
+    p = problem(55, True, 128, 4, 32, 16, 64, B=16, L=4)
+    pool, batch = G.to_device(p)
+    expect = G.clone_pool(pool)
+    elen = torch.empty((16, 4, 2), dtype=torch.int32, device="cuda")
+    G.ctx().zp_compress(expect, batch, elen)
+    G.ctx().zp_compress(pool, batch, getattr(batch, into))
+    G.ctx().zp_sync_status()
+    assert torch.equal(getattr(batch, into), elen)
+    assert torch.equal(pool.k.view(torch.int16), expect.k.view(torch.int16)) and torch.equal(pool.v.view(torch.int16), expect.v.view(torch.int16))
