@@ -92,14 +92,17 @@ typedef struct {
                                    w <= k_h <= min((N_max-1) b, valid_len + b); NULL = (N_max-1) b */
 } zp_batch;
 
-/* Context: owns a few device status words and the last error text.  Needs a GPU. */
+/* Context: owns a few device status words, the workspaces described at zp_scratch_bytes (96 MB of device memory, if there is
+   room) and the last error text.  Needs a GPU and belongs to the one that is current at zp_create: calls on streams of another
+   GPU use no workspace and take one launch. */
 zp_status zp_create(zp_ctx **out);
 void zp_destroy(zp_ctx *ctx);
 const char *zp_last_error(const zp_ctx *ctx); /* ctx may be NULL: text of the last failed zp_create/zp_plan */
 
 /* Device scratch zp_score / zp_compress need from the caller beyond inputs and outputs for this shape: none.  Calls of few
-   units use workspaces of the context (96 MB, allocated by zp_create if there is room; one per stream, calls on more than
-   four streams at once share them and are ordered behind each other on the device). */
+   units use workspaces of the context (four of 24 MB; one per stream, calls on more than four streams at once share them and
+   are ordered behind each other on the device).  Such a call waits on the device for the workspace's last call and records an
+   event; under graph capture, without workspaces and in zp_compress_static every call is one launch. */
 size_t zp_scratch_bytes(const zp_pool *pool, const zp_batch *batch);
 
 /* Tuning / test switches.  ZP_OPT_SPLIT: -1 (default) and 0 are accepted and change nothing; 1 asked for a kernel in which

@@ -234,6 +234,9 @@ static int split_parts(const zp_ctx *ctx, const zp::Args &a, Path path, const zp
     const long long units = (long long)a.B * a.L_slab * a.h_kv;
     if (path != PATH_MFMA || geo.NP != 1 || a.ex || !ctx->slot[0].mem || units <= 0 || a.T_max < 512 || !few_units(ctx, units)) return 0;
     if (workspace_bytes(a, geo, units) > kSlotBytes || overlaps_tables(a, units)) return 0;
+    int dev = -1;                                              // workspaces and events belong to the context's GPU
+    if ((s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) != hipSuccess) (void)hipGetLastError();
+    if (dev != ctx->device) return 0;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
         (void)hipGetLastError();                               // not the launch's error

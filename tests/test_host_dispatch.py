@@ -1,0 +1,127 @@
+"""The library's host code without a GPU: which launches a call takes.  zp_api.hip and zp_kernels.hip are compiled for the host alone
+and linked against stand-ins of the HIP runtime (tests/host_stub.hip) that log every launch instead of running it."""
+import ctypes
+import os
+import re
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import pytest
+
+from paper_2603_08743_amd import binding
+from paper_2603_08743_amd.build import CSRC, FLAGS
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ADDRESS = {n: 0x100000000000 + (i << 36) for i, n in enumerate(("k", "v", "q", "tbl", "dst", "nb", "slot", "vl", "keep", "len", "scores", "idx"))}
+
+
+@pytest.fixture(scope="session")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host")
+    srcs = [os.path.join(CSRC, "zp_api.hip"), os.path.join(CSRC, "zp_kernels.hip"), os.path.join(HERE, "host_stub.hip")]
+    flags = [f for f in FLAGS if f != "-O3"] + ["-O1", "--offload-host-only"]
+    objs = [str(d / ("%d.o" % i)) for i in range(len(srcs))]
+    compile_one = lambda so: subprocess.run(["hipcc", *flags, "-c", so[0], "-o", so[1]], capture_output=True, text=True)  # noqa: E731
+    with ThreadPoolExecutor() as ex:
+        for r in ex.map(compile_one, zip(srcs, objs)):
+            assert r.returncode == 0, r.stderr[-2000:]
+    fatbins = set(re.findall(r"__hip_fatbin\w*", subprocess.run(["nm", "-u", *objs], capture_output=True, text=True).stdout))
+    so = str(d / "libzp_host.so")
+    r = subprocess.run(["g++", "-shared", "-o", so, *objs, "-Wl,-Bsymbolic", *["-Wl,--defsym=%s=stub_blob" % f for f in fatbins], "-lpthread"],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    h = ctypes.CDLL(so)
+    h.stub_log.restype = ctypes.c_char_p
+    h.zp_last_error.restype = ctypes.c_char_p
+    h.zp_last_error.argtypes = [ctypes.c_void_p]
+    h.zp_destroy.restype = None
+    h.zp_destroy.argtypes = [ctypes.c_void_p]
+    return h
+
+
+class Caller:
+    """One context; calls with addresses that nothing reads."""
+
+    def __init__(self, lib, **state):
+        self.lib = lib
+        for what in ("device", "stream_device", "capturing", "no_memory"):
+            lib.stub_set(what.encode(), state.get(what, 0))
+        self.h = ctypes.c_void_p()
+        assert lib.zp_create(ctypes.byref(self.h)) == 0
+
+    def set(self, what, value):
+        self.lib.stub_set(what.encode(), value)
+
+    def call(self, name, units=64, T=4112, d=128, G=4, w=64, b=16, dtype="bf16", stream=0, at=None, extras=None):
+        """units requests of one layer and one kv head; returns the log lines."""
+        A = dict(ADDRESS, **(at or {}))
+        N = T // b
+        p = binding._Pool(A["k"], A["v"], A["q"], 0, 1, 1 << 20, b, 1, G, d, units, w, binding.ZP_BF16 if dtype == "bf16" else binding.ZP_F32)
+        t = binding._Batch(units, N, N, 1, A["tbl"], None, A["nb"], A["slot"], A["vl"], A["keep"])
+        P, Bt, s = ctypes.byref(p), ctypes.byref(t), ctypes.c_void_p(stream)
+        at_ = lambda n: ctypes.c_void_p(A[n])  # noqa: E731
+        self.lib.stub_clear()
+        if name == "compress":
+            rc = self.lib.zp_compress(self.h, P, Bt, at_("len"), None, None, s)
+        elif name == "compress_ex":
+            rc = self.lib.zp_compress_ex(self.h, P, Bt, ctypes.byref(extras), at_("len"), None, None, s)
+        elif name == "static":
+            rc = self.lib.zp_compress_static(P, Bt, at_("len"), s)
+        elif name == "score":
+            rc = self.lib.zp_score(self.h, P, Bt, at_("scores"), s)
+        elif name == "select":
+            rc = self.lib.zp_select_topk(self.h, at_("scores"), ctypes.c_int32(T), P, Bt, at_("idx"), at_("len"), s)
+        else:
+            rc = self.lib.zp_compact_kv(self.h, P, Bt, at_("idx"), at_("len"), s)
+        assert rc == 0, self.lib.zp_last_error(self.h)
+        return self.lib.stub_log().decode().splitlines()
+
+    def launches(self, *a, **k):
+        return [l for l in self.call(*a, **k) if l.startswith("launch")]
+
+
+def test_few_units_take_three_launches_and_large_calls_one(lib):
+    c = Caller(lib)
+    log = c.launches("compress")
+    assert len(log) == 3 and "phase 1" in log[0] and "phase 2" in log[1] and "unit_sliced" in log[2]
+    assert len(c.launches("score")) == 2
+    assert len(c.launches("compress", units=512)) == 1
+    assert len(c.launches("static")) == 2                                      # the fill kernel and one launch
+
+
+def test_no_workspace_or_a_capture_means_one_launch(lib):
+    assert len(Caller(lib, no_memory=1).launches("compress")) == 1
+    c = Caller(lib)
+    c.set("capturing", 1)
+    log = c.call("compress")
+    assert len(log) == 1 and "phase 0" in log[0]                               # no wait, no event
+
+
+@pytest.mark.parametrize("stream", [0, 7])
+def test_calls_on_another_gpu_leave_the_workspaces_alone(lib, stream):
+    """The workspaces and events belong to the GPU the context was created on."""
+    c = Caller(lib, device=0, stream_device=0)
+    assert len(c.launches("compress", stream=stream)) == 3
+    c.set("device", 1)
+    c.set("stream_device", 1)
+    for name in ("compress", "score"):
+        log = c.call(name, stream=stream)
+        assert len(log) == 1 and "phase 0" in log[0], log
+
+
+@pytest.mark.parametrize("name,split", [("vl", True), ("keep", True), ("nb", False), ("slot", False), ("tbl", False)])
+def test_len_out_inside_the_batch_arrays(lib, name, split):
+    """valid_len and keep are read once per call; a table that every launch reads again keeps the call to one launch."""
+    log = Caller(lib).launches("compress", at={"len": ADDRESS[name]})
+    assert len(log) == (3 if split else 1)
+
+
+def test_workspaces_by_stream(lib):
+    """A stream keeps its workspace; a fifth stream takes the first one's and waits for it on the device."""
+    c = Caller(lib)
+    event = lambda log: [int(l.split()[1]) for l in log if l.startswith("record")]  # noqa: E731
+    first = [event(c.call("compress", stream=s)) for s in (1, 2, 3, 4)]
+    assert len({e[0] for e in first}) == 4
+    log = c.call("compress", stream=5)
+    assert event(log) == first[0] and "wait %d stream 5" % first[0][0] == log[0]
+    assert event(c.call("compress", stream=3)) == first[2]
