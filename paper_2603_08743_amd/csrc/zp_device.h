@@ -602,13 +602,16 @@ __device__ inline void redundancy_mfma(const Args &a, const Unit &u, const int *
 // column r is the sum of row r before zeroing, and what was zeroed in row r is taken off in a pass of its own (waves go
 // through the columns that have a zeroed entry only).  inv, zr, zv: LDS, by logical position: inverse norm (0: not live),
 // row zeroed in the column (-1: none) and its value.
-// Row fragments come from L2 (the unit's keys have just been swept), with few waves (PF) those of the next tile requested
+// Row fragments come from L2 (the unit's keys have just been swept), with few waves (FEW) those of the next tile requested
 // before the current tile is worked on.  Before, one thread per key took b dot products one element at a time: 345 ms per launch for 1152 units
-// of 2304 positions in blocks of 256 (d 128, bf16), now 1.71 ms.
-template <int ROWB, int DT, bool PAD, bool PF>
+// of 2304 positions in blocks of 256 (d 128, bf16), now 1.71 ms.  Eight waves have 128 registers each and hold the column
+// group only, rows of 192 and 256 bytes come piece by piece (512 units of 4112 positions, d 128, w 64: blocks of 64 1065 -> 1007 us,
+// of 256 1540 -> 1522 us against both held and 21 registers spilled).
+template <int ROWB, int DT, bool PAD, bool FEW>
 __device__ inline void redundancy_blocks(const Args &a, const Unit &u, const int *tbl, float *rs, float *inv, int *zr, float *zv) {
     constexpr int KK = ROWB / 32;
-    constexpr bool HOLD = ROWB <= 256;                           // fragments of three row sets fit the registers
+    constexpr bool HOLD = ROWB <= 256;                           // a column group's fragments fit the registers ...
+    constexpr bool HOLD_ROWS = HOLD && (FEW || ROWB <= 128);     // ... beside those of a row group (two with FEW)
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6, l32 = lane & 31, hf = lane >> 5;
     const int b = a.b, stale_hi = (u.N - 1) * b;
     const float inv_len = 1.0f / (float)u.Tv;
@@ -629,6 +632,16 @@ __device__ inline void redundancy_blocks(const Args &a, const Unit &u, const int
                 y = *(const u32x4 *)(cp + kk * 32 + hf * 16);
             }
             acc = mma32<DT>(x, y, acc);
+        }
+        return acc;
+    };
+    auto gram_rows = [&](const char *rp, const u32x4 (&col)[HOLD ? KK : 1]) {
+        f32x16 acc = zero16;
+#pragma unroll
+        for (int kk = 0; kk < (HOLD ? KK : 0); kk++) {
+            u32x4 x = {0u, 0u, 0u, 0u};
+            if (!PAD || kk * 32 + hf * 16 < a.row_bytes) x = *(const u32x4 *)(rp + kk * 32 + hf * 16);
+            acc = mma32<DT>(x, col[kk], acc);
         }
         return acc;
     };
@@ -663,14 +676,14 @@ __device__ inline void redundancy_blocks(const Args &a, const Unit &u, const int
         }
         return it;
     };
-    auto load_group = [&](int it, int step, u32x4 (&f)[HOLD ? KK : 1]) {   // rows of the group `step` places after the item's own
+    auto load_group = [&](int it, int step, u32x4 (&f)[HOLD_ROWS ? KK : 1]) {   // rows of the group `step` places after the item's own
         const int blk = it / ncg, cg = it - blk * ncg, rg = cg + step < ncg ? cg + step : cg + step - ncg;
         const int r = rg * 32 + l32;
         const char *rp = row_ptr(blk * b + (r < b ? r : b - 1));
-        if constexpr (HOLD) load_row<ROWB, PAD>(rp, hf, a.row_bytes, f);
+        if constexpr (HOLD_ROWS) load_row<ROWB, PAD>(rp, hf, a.row_bytes, f);
         return rp;
     };
-    u32x4 cur[HOLD ? KK : 1], nxt[HOLD ? KK : 1], col[HOLD ? KK : 1];
+    u32x4 cur[HOLD_ROWS ? KK : 1], nxt[HOLD_ROWS ? KK : 1], col[HOLD ? KK : 1];
     int it = wanted(wv);
     const char *cp = nullptr, *rp = nullptr, *rpn = nullptr;
     if (it < items) rp = load_group(it, 0, cur);
@@ -683,21 +696,22 @@ __device__ inline void redundancy_blocks(const Args &a, const Unit &u, const int
         float csum = 0.f, lastv = 0.f;
         int last = -1;
         cp = rp;
-        if constexpr (HOLD) {
+        if constexpr (HOLD_ROWS) {
 #pragma unroll
             for (int kk = 0; kk < KK; kk++) col[kk] = cur[kk];
-        }
+        } else if constexpr (HOLD) load_row<ROWB, PAD>(cp, hf, a.row_bytes, col);
 #pragma unroll 1
         for (int step = 0; step < ncg; step++) {
-            if (PF) {
+            if (FEW) {
                 if (step + 1 < ncg) rpn = load_group(it, step + 1, nxt);
                 else if (itn < items) rpn = load_group(itn, 0, nxt);
             }
             f32x16 acc = zero16;
-            if constexpr (HOLD) {
+            if constexpr (HOLD_ROWS) {
 #pragma unroll
                 for (int kk = 0; kk < KK; kk++) acc = mma32<DT>(cur[kk], col[kk], acc);
-            } else acc = gram_stream(rp, cp);
+            } else if constexpr (HOLD) acc = gram_rows(rp, col);
+            else acc = gram_stream(rp, cp);
             const int rg = cg + step < ncg ? cg + step : cg + step - ncg;
             const int r0 = rg * 32 + 4 * hf;                     // register i: row r0 + 8*(i/4) + i%4
             float mx = -INFINITY;
@@ -717,9 +731,9 @@ __device__ inline void redundancy_blocks(const Args &a, const Unit &u, const int
                     if (acc[i] > a.p_thr && r > last && r < b) { last = r; lastv = acc[i]; }
                 }
             }
-            if (PF) {
+            if (FEW) {
                 rp = rpn;
-                if constexpr (HOLD) {
+                if constexpr (HOLD_ROWS) {
 #pragma unroll
                     for (int kk = 0; kk < KK; kk++) cur[kk] = nxt[kk];
                 }
@@ -831,7 +845,8 @@ __device__ __forceinline__ void block_row_sums(const Args &a, const Unit &u, con
 }
 
 // ROWB > 0: called from the matrix-core kernel for rows of up to ROWB bytes; ROWB = 0: generic kernel.  Element type DT.
-// REF 2: a launch whose similarity tiles came from sweep 2 (EX_RED_FUSED), REF 1: any other with refinements.
+// REF 1: global score and pooling; REF 2: a launch whose similarity tiles came from sweep 2 (EX_RED_FUSED); REF 3: any other
+// with redundancy.
 template <int ROWB, int DT, bool PAD, int REF, int NW>
 __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, const int *tbl, Misc *misc) {
     const int tid = threadIdx.x, nt = blockDim.x;
@@ -870,7 +885,7 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
         for (int j = tid; j < u.Tv; j += nt) S[live_to_pos(u, a, j)] = tmp[j];
         __syncthreads();
     }
-    if (a.ex & EX_RED) {
+    if constexpr (REF != 1) if (a.ex & EX_RED) {
         if constexpr (REF == 2) {                                // the live prefix was done from the key tiles of sweep 2
             tmp = (float *)(smem + a.off_R);
             redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, true);

@@ -50,9 +50,11 @@ template <int ROWB> struct KTile {
     static constexpr int CPR = ROWB / 16;         // 16-byte pieces per key row
 };
 
-// REF: 0 no score refinements in this launch, 1 refinements in the tail, 2 (block size 16, RB = 1, unpadded bf16 rows) the
-// lightning redundancy as well, its similarity tiles of the live prefix taken from the key tiles of sweep 2 (otherwise
-// the keys are read a third time in the tail).
+// REF: 0 no score refinements in this launch, 1 global score and pooling in the tail, 3 the lightning redundancy as well, 2
+// (block size 16, RB = 1, unpadded bf16 rows) its similarity tiles of the live prefix taken from the key tiles of sweep 2
+// (with 3 the keys are read a third time in the tail).  With the redundancy code in it an eight-wave kernel has no registers
+// left, so launches without redundancy do not carry it: 512 units of 4112 positions (d 128, G 4, w 64) with global score and
+// pooling took 644 us with 21 spilled registers and take 622 us with none.
 // MP: the query blocks take several passes over the keys (NP groups of NW * RB blocks), S collecting their sums.
 template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP, int PH = 0>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP_WPE(NW, RB, ROWB)))) unit_mfma(const Args a) {
@@ -479,12 +481,13 @@ static hipError_t launch_one(const Args &a, int units, hipStream_t s) {
     return hipGetLastError();
 }
 
-// ALL_REF: the refinement variants of a geometry (REF 1, and 2 where it exists); otherwise the plain one
+// ALL_REF: the refinement variants of a geometry (REF 1, 3, and 2 where it exists); otherwise the plain one
 template <int ROWB, int RB, int NW, int GT, bool ALL_REF>
 static hipError_t launch_ref(const Args &a, int units, hipStream_t s) {
     if constexpr (!ALL_REF) return launch_one<1, ROWB, false, RB, NW, GT, 0, false>(a, units, s);
     else {
         if constexpr (RB == 1) if (a.ex & EX_RED_FUSED) return launch_one<1, ROWB, false, RB, NW, GT, 2, false>(a, units, s);
+        if (a.ex & EX_RED) return launch_one<1, ROWB, false, RB, NW, GT, 3, false>(a, units, s);
         return launch_one<1, ROWB, false, RB, NW, GT, 1, false>(a, units, s);
     }
 }
@@ -521,9 +524,9 @@ static hipError_t launch_d(const Args &a, int units, int NW, int RB, hipStream_t
 template <int DT, int ROWB>
 static hipError_t launch_pad(const Args &a, int units, int NW, hipStream_t s) {
     const bool ref = (a.ex & (EX_GLOBAL | EX_POOL | EX_RED)) != 0;
-    if (NW == 2) return ref ? launch_one<DT, ROWB, true, 1, 2, 0, 1, false>(a, units, s) : launch_one<DT, ROWB, true, 1, 2, 0, 0, false>(a, units, s);
-    if (NW == 4) return ref ? launch_one<DT, ROWB, true, 1, 4, 0, 1, false>(a, units, s) : launch_one<DT, ROWB, true, 1, 4, 0, 0, false>(a, units, s);
-    if (NW == 8) return ref ? launch_one<DT, ROWB, true, 1, 8, 0, 1, true>(a, units, s) : launch_one<DT, ROWB, true, 1, 8, 0, 0, true>(a, units, s);
+    if (NW == 2) return ref ? launch_one<DT, ROWB, true, 1, 2, 0, 3, false>(a, units, s) : launch_one<DT, ROWB, true, 1, 2, 0, 0, false>(a, units, s);
+    if (NW == 4) return ref ? launch_one<DT, ROWB, true, 1, 4, 0, 3, false>(a, units, s) : launch_one<DT, ROWB, true, 1, 4, 0, 0, false>(a, units, s);
+    if (NW == 8) return ref ? launch_one<DT, ROWB, true, 1, 8, 0, 3, true>(a, units, s) : launch_one<DT, ROWB, true, 1, 8, 0, 0, true>(a, units, s);
     return hipErrorInvalidConfiguration;
 }
 
