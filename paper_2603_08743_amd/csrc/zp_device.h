@@ -80,6 +80,9 @@ __device__ __forceinline__ int unit_of_block(int bid, int n, int mode) {
 
 // Decode the unit and check its scalar metadata (identical for every thread and every workgroup
 // that looks at the unit).  Returns 0 or the reason the unit must be skipped.
+// FIXED: several workgroups of a unit come through here in the launch that writes len_out, and a caller may pass valid_len or keep
+// as len_out: the two values are then those an earlier launch of the call has read.
+template <bool FIXED>
 __device__ inline int unit_scalars(const Args &a, int unit, Unit &u) {
     u.unit = unit;
     u.h = unit % a.h_kv;
@@ -93,11 +96,9 @@ __device__ inline int unit_scalars(const Args &a, int unit, Unit &u) {
     u.Tv = u.vl + a.b;
     if (u.N < a.N_max || u.N > a.max_blocks) return BAD_NUM_BLOCKS;
     const int idx = (u.n * a.L + a.layer0 + u.ls) * a.h_kv + u.h;
-    // Several workgroups of a unit come through here in the launch that writes len_out, and a caller may pass valid_len or keep as
-    // len_out: the values are then those an earlier launch of the call has read.
-    const int2 fixed = a.unit_in ? a.unit_in[unit] : make_int2(0, 0);
-    if (a.unit_in || a.valid_len) {
-        u.vl = a.unit_in ? fixed.x : a.valid_len[idx];
+    const bool fixed = FIXED && a.unit_in;
+    if (fixed || a.valid_len) {
+        u.vl = fixed ? a.unit_in[unit].x : a.valid_len[idx];
         if (u.vl < 0 || u.vl > (u.N - 1) * a.b) return BAD_VALID_LEN;
     }
     u.Tv = u.vl + a.b;
@@ -106,7 +107,7 @@ __device__ inline int unit_scalars(const Args &a, int unit, Unit &u) {
         u.k = a.len_in[unit];
         if (u.k > a.budget) return BAD_KEEP;
     } else {
-        if (a.unit_in) u.k = fixed.y;
+        if (fixed) u.k = a.unit_in[unit].y;
         else if (a.keep) u.k = a.keep[idx];
         const int cap = a.budget < u.Tv ? a.budget : u.Tv;
         if (u.k < a.w || u.k > cap) return BAD_KEEP;
@@ -120,9 +121,10 @@ __device__ inline int unit_scalars(const Args &a, int unit, Unit &u) {
 
 // Decode the unit, check its metadata, stage both block tables in LDS.
 // Returns false (for every thread alike) when the unit must be skipped.
+template <bool FIXED = false>
 __device__ inline bool unit_setup(const Args &a, int unit, Unit &u, int *tbl, int *dst, Misc *misc) {
     const int tid = threadIdx.x, nt = blockDim.x;
-    int bad = unit_scalars(a, unit, u);
+    int bad = unit_scalars<FIXED>(a, unit, u);
     if (tid == 0) misc->bad = bad;
     __syncthreads();
     if (!bad) {

@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(1024) unit_sliced(const Args a) {
     Misc *misc = (Misc *)(smem + a.off_misc);
     const int v = unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map);
     Unit u;
-    if (!unit_setup(a, v / a.slices, u, tbl, dst, misc)) return;
+    if (!unit_setup<true>(a, v / a.slices, u, tbl, dst, misc)) return;
     unit_tail<0, 1, false, 0, 16, true>(a, u, smem, tbl, dst, misc, v % a.slices);
 }
 
