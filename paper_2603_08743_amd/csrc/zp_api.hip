@@ -245,13 +245,19 @@ static int split_parts(const zp_ctx *ctx, const zp::Args &a, Path path, const zp
     return cap == hipStreamCaptureStatusNone ? zp::segments_of(geo.RB) : 0;   // a graph may run beside anything: no shared workspace
 }
 
-// Row-moving workgroups per unit: K and V apart, rows cut into 128-byte (64-byte) pieces while that makes no more than two
-// workgroups per compute unit.  64 units that move 4096 rows of 256 bytes in K and V: 64 us with the selection, 3.9 TB/s.
+// Row-moving workgroups per unit: K and V apart, rows cut into the shortest pieces (from 128 bytes on, 64 where those do not divide
+// the row) that make no more workgroups than compute units.  A workgroup of sixteen waves at 67 registers has a compute unit to
+// itself, so more of them take turns and every turn pays for the set-up and a selection of its own.  Measured (rows of 256 bytes, d 128,
+// G 4, w 32, 1040 positions, whole call) with four pieces against two: 96 units 66 against 59 us, 128 units 77 against 72 us; rows of
+// 512 bytes (fp32, 64 units, 512 positions) with eight against two 82 against 80 us; at 64 units of 256 bytes all four pieces
+// run at once: 4112 rows of K and V in 64 us with the selection, 3.9 TB/s.  64 registers for two workgroups per
+// compute unit gave 6 us at 160 to 192 units below 1040 positions and lost up to 2.7 % at 4112 and more.
 static void pick_slices(const zp_ctx *ctx, zp::Args *a, int units) {
     a->slices = 2;
     a->slice_bytes = a->row_bytes;
-    for (int piece = 128; piece >= 64; piece >>= 1)
-        if (a->row_bytes % piece == 0 && a->row_bytes > piece && (long long)units * 2 * (a->row_bytes / piece) <= 2 * ctx->n_cu) {
+    const auto fits = [&](int piece) { return a->row_bytes % piece == 0 && a->row_bytes > piece && (long long)units * 2 * (a->row_bytes / piece) <= ctx->n_cu; };
+    for (const int piece : {128, 256, 512, 64})
+        if (fits(piece)) {
             a->slices = 2 * (a->row_bytes / piece);
             a->slice_bytes = piece;
             break;

@@ -125,3 +125,18 @@ def test_workspaces_by_stream(lib):
     log = c.call("compress", stream=5)
     assert event(log) == first[0] and "wait %d stream 5" % first[0][0] == log[0]
     assert event(c.call("compress", stream=3)) == first[2]
+
+
+@pytest.mark.parametrize("units", [1, 8, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 192])
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (96, "bf16"), (24, "bf16"), (256, "bf16"), (128, "f32"), (256, "f32"), (160, "bf16")])
+def test_row_moving_workgroups_run_at_once(lib, units, d, dtype):
+    """A row-moving workgroup fills a compute unit: rows are cut up only while all pieces of all units run at the same time."""
+    row = d * (2 if dtype == "bf16" else 4)
+    for name in ("compact", "compress"):
+        last = Caller(lib).launches(name, units=units, d=d, dtype=dtype, T=2064, w=4)[-1]
+        slices, piece = (int(x) for x in re.search(r"slices (\d+) slice_bytes (\d+)", last).groups())
+        assert slices * piece == 2 * row and piece % 16 == 0
+        assert units * slices <= 256 or slices == 2
+        assert slices == 2 or piece >= 64
+    if row == 256:
+        assert slices == (4 if units <= 64 else 2)
