@@ -206,14 +206,39 @@ extern "C" size_t zp_scratch_bytes(const zp_pool *pool, const zp_batch *batch) {
 }
 
 // With one workgroup per unit, a launch of fewer units than compute units leaves the rest idle, and one unit's two sweeps,
-// selection and row moving follow each other on its own.  Up to three quarters of the compute units such calls take three
-// launches instead: sweep 1 and sweep 2 with up to eight workgroups per unit (a run of its key tiles each), then selection and
-// row moving with the rows cut into slices.  Measured (256 compute units): 64 units of 4112 positions (d 128, G 4, w 64)
-// 266 -> 120 us; 72 units of up to 1248 (d 96, w 20) 154 -> 75 us; 128 fp32 units of 1040 295 -> 200 us; staged, 192 units of up
-// to 4128 310 -> 228 us.  At 256 units of 4112 the one launch is the better one (351 us against 408 us: its phases overlap
-// between workgroups), at 448 of 2064 more so (276 against 403 us), and below 512 positions three launches cost more than they
-// share out (16 positions: 14 us against 28 us).
+// selection and row moving follow each other on its own.  Row moving (and a selection of its own) is cut into slices up to three
+// quarters of the compute units: staged select and compact of 192 units 52 -> 50 us at 272 positions, 437 -> 343 us at 4112.
 static bool few_units(const zp_ctx *ctx, long long units) { return units <= ctx->n_cu * 3 / 4; }
+
+// Whether scoring in two launches with several workgroups per unit (`whole`: then selection and row moving in a third) beats one
+// launch.  A launch more costs its set-up once per workgroup and its wait for the slowest one, and the wider a unit's workgroup,
+// the fewer units fill the chip by themselves.  So the line is drawn on positions against waves in one launch (units x waves per
+// workgroup); the measurements below are one launch against three in us, d 128, G 4, bf16, 256 compute units:
+//   eight waves (w 64):   64 units   4112           265:122
+//                                     768 positions  55: 48      512  39: 46
+//                         96         1040            80: 75      768  60: 63
+//                        128         2064           151:135     1040  84: 92
+//                        160 or 192  up to 8208 never worth it (4112: 298:314, 316:344)
+//   four (w 32):   128 or fewer 512  52: 51;   160  1040 108: 97  768 78: 82;   192  1040 111:108  768 82: 91
+//   two (w 16):    192  768  92: 82   512 63: 67;    one (w 4): 192  512  96: 68
+//   several blocks per wave (w 112), four workgroups per unit that fill a compute unit each:
+//                   64   512  53: 47;    96  1040 105: 99   768 79: 82;   128  1040 109:107;   160 4112 381:408
+//   two staged scoring launches against one, the row moving being sliced either way, need 8/5 of the positions:
+//                  128 of eight waves  2064 211:209  1040 118:131;   192 of four  2064 228:219  1040 125:131
+// Rows of 128 bytes (d 64) have less to share out, fp32 and other long rows more (eight waves, fp32, 128 units: 512 183:172).
+static bool split_pays(int n_cu, long long units, int T, const zp::MfmaGeo &geo, bool f32, bool whole) {
+    const long long u = units * 256 / n_cu;                    // the same share of 256 compute units
+    if (T < 512) return false;
+    if (geo.RB > 1 && u <= 64) return T >= (geo.rowb <= 128 ? 768 : 512);
+    const bool heavy = geo.RB > 2 || geo.rowb > 256;
+    if (u > 128) {                                             // two rounds of row-moving workgroups
+        if (geo.NW == 8) return heavy ? T >= 16 * u : !whole && T >= 24 * u;
+        if (geo.NW > 1 && geo.rowb <= 512 && T < 768) return false;
+    }
+    const long long need = u * geo.NW * (whole ? 5 : 8) / 4 * (f32 ? 5 : heavy ? 8 : 10) / 10;
+    const bool early = heavy || geo.NW <= 2 || (geo.NW == 4 && geo.rowb > 128 && whole);
+    return T >= need && (early || T >= 640);
+}
 
 // Workspace of a call: partial sums of sweep 1, the units' scalars, the scores.
 static size_t seg_bytes(const zp::MfmaGeo &geo, long long units) { return (size_t)units * ZP_SEGMENTS * geo.NW * geo.RB * 32 * sizeof(float2); }
@@ -229,10 +254,12 @@ static bool overlaps_tables(const zp::Args &a, long long units) {
            meets(a.dst_table, (long long)a.B * (a.N_max - 1));
 }
 
-// Workgroups per unit of the two scoring launches (0: one launch does everything).  Four instead of eight: 125, 79, 190 and 234 us.
+// Workgroups per unit of the two scoring launches (0: one launch does everything).
 static int split_parts(const zp_ctx *ctx, const zp::Args &a, Path path, const zp::MfmaGeo &geo, hipStream_t s) {
     const long long units = (long long)a.B * a.L_slab * a.h_kv;
-    if (path != PATH_MFMA || geo.NP != 1 || a.ex || !ctx->slot[0].mem || units <= 0 || a.T_max < 512 || !few_units(ctx, units)) return 0;
+    if (path != PATH_MFMA || geo.NP != 1 || a.ex || !ctx->slot[0].mem || units <= 0 || !few_units(ctx, units) ||
+        !split_pays(ctx->n_cu, units, a.T_max, geo, a.dtype == 0, (a.stages & zp::STAGE_SELECT) != 0))
+        return 0;
     if (workspace_bytes(a, geo, units) > kSlotBytes || overlaps_tables(a, units)) return 0;
     int dev = -1;                                              // workspaces and events belong to the context's GPU
     if ((s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) != hipSuccess) (void)hipGetLastError();

@@ -140,3 +140,42 @@ def test_row_moving_workgroups_run_at_once(lib, units, d, dtype):
         assert slices == 2 or piece >= 64
     if row == 256:
         assert slices == (4 if units <= 64 else 2)
+
+
+# one launch against several, microseconds measured on 256 compute units (d 128, G 4, bf16 unless stated): which of the two is taken
+MEASURED = [
+    # call, shape, units, positions, one launch, several
+    ("compress", dict(w=64), 8, 768, 43, 34), ("compress", dict(w=64), 8, 512, 31, 33), ("compress", dict(w=64), 64, 768, 55, 48),
+    ("compress", dict(w=64), 64, 512, 39, 46), ("compress", dict(w=64), 96, 1040, 80, 75), ("compress", dict(w=64), 96, 768, 60, 63),
+    ("compress", dict(w=64), 128, 2064, 151, 135), ("compress", dict(w=64), 128, 1040, 84, 92), ("compress", dict(w=64), 160, 4112, 298, 314),
+    ("compress", dict(w=64), 160, 512, 46, 88), ("compress", dict(w=64), 192, 512, 47, 98), ("compress", dict(w=64), 192, 2064, 164, 203),
+    ("compress", dict(w=32), 64, 512, 43, 39), ("compress", dict(w=32), 160, 1040, 108, 97), ("compress", dict(w=32), 160, 768, 78, 82),
+    ("compress", dict(w=32), 192, 768, 82, 91), ("compress", dict(w=32), 192, 1040, 111, 108), ("compress", dict(w=32), 192, 2064, 208, 173),
+    ("compress", dict(w=16), 192, 768, 92, 82), ("compress", dict(w=16), 192, 512, 63, 67), ("compress", dict(w=4), 192, 512, 96, 68),
+    ("compress", dict(w=112), 64, 512, 53, 47), ("compress", dict(w=112), 96, 768, 79, 82), ("compress", dict(w=112), 96, 1040, 105, 99),
+    ("compress", dict(w=112), 128, 2064, 195, 162), ("compress", dict(w=112), 160, 4112, 381, 408),
+    ("compress", dict(w=128, G=8), 192, 4112, 826, 734), ("compress", dict(w=128, G=8), 128, 512, 116, 149),
+    ("compress", dict(w=32, d=64), 160, 768, 50, 56), ("compress", dict(w=32, d=64), 64, 768, 40, 34), ("compress", dict(w=32, d=64), 96, 512, 30, 36),
+    ("compress", dict(w=16, d=64), 192, 512, 40, 51), ("compress", dict(w=112, d=64), 64, 512, 35, 38), ("compress", dict(w=112, d=64), 64, 768, 51, 41),
+    ("compress", dict(w=20, d=96, G=3, b=24), 192, 1040, 128, 114), ("compress", dict(w=20, d=96, G=3), 192, 512, 62, 76),
+    ("compress", dict(w=32, dtype="f32"), 128, 512, 147, 107), ("compress", dict(w=8, d=256, dtype="f32"), 192, 512, 307, 211),
+    ("compress", dict(w=64, dtype="f32"), 8, 512, 158, 63), ("compress", dict(w=64, d=256), 96, 768, 119, 111),
+    ("score", dict(w=64), 64, 1040, 105, 96), ("score", dict(w=64), 96, 1040, 112, 114), ("score", dict(w=64), 128, 2064, 211, 209),
+    ("score", dict(w=64), 160, 2064, 220, 232), ("score", dict(w=64), 160, 4112, 417, 400), ("score", dict(w=32), 192, 1040, 125, 131),
+    ("score", dict(w=32), 192, 2064, 228, 219), ("score", dict(w=32), 96, 512, 57, 64), ("score", dict(w=16), 192, 512, 71, 77),
+    ("score", dict(w=16), 192, 768, 101, 96), ("score", dict(w=112), 64, 512, 70, 66), ("score", dict(w=112), 96, 1040, 136, 139),
+]
+
+
+@pytest.mark.parametrize("call,shape,units,T,one,several", MEASURED)
+def test_the_faster_way_is_taken_on_both_sides_of_the_line(lib, call, shape, units, T, one, several):
+    b = shape.get("b", 16)
+    n = len(Caller(lib).launches(call, units=units, T=T // b * b, **shape))
+    assert n == (1 if one < several else 3 if call == "compress" else 2)
+
+
+def test_no_more_than_three_quarters_of_the_compute_units(lib):
+    c = Caller(lib)
+    assert [len(c.launches("compress", units=u, w=4)) for u in (192, 193)] == [3, 1]
+    assert [c.launches("select", units=u)[0].split()[1] for u in (192, 193)] == ["unit_sliced", "unit_generic"]
+    assert [c.launches("compact", units=u)[0].split()[1] for u in (192, 193)] == ["unit_sliced", "unit_generic"]
