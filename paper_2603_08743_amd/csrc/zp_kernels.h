@@ -88,8 +88,10 @@ hipError_t launch_unit_sliced(const Args &a, int units, hipStream_t s);
 // The keys of a unit are cut into at most ZP_SEGMENTS runs of whole tiles, a function of their number alone.  Sweep 1 sums
 // every run by itself and the runs are put together in ascending order, whichever workgroups they ran in: a call gives the
 // same bits with one workgroup per unit and with several.
-// One run costs a second look at its first 32 keys.  Four runs where a wave holds several query blocks: such a workgroup fills a
-// compute unit, so 64 units have their share with four (384 units of 8208 positions, G 5, w 128, one launch: eight runs cost 0.9 %).
+// One run costs a maximum over its first 32 keys (FIRST_MAX in zp_mfma.h) or a second look at them, and a merge: between nothing and
+// 1.5 % of a launch against one run, most with several blocks per wave.  Four runs where a wave holds several query blocks: such a
+// workgroup fills a compute unit, so 64 units have their share with four (384 units of 8208 positions, G 5, w 128, one launch with
+// the second look: eight runs cost 0.9 %).
 #define ZP_SEGMENTS 8
 constexpr __host__ __device__ int segments_of(int RB) { return RB > 1 ? 4 : ZP_SEGMENTS; }
 // Geometry of the matrix-core kernel for a launch: waves per workgroup, 32-row query blocks per wave, passes over the keys,

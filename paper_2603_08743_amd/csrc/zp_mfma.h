@@ -59,6 +59,11 @@ template <int ROWB> struct KTile {
 template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP, int PH = 0>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP_WPE(NW, RB, ROWB)))) unit_mfma(const Args a) {
     constexpr bool RED = REF == 2;
+    // A segment starts with the maximum of its first 32 keys as reference, not with a subtile that is redone: same bits.  1664 units of
+    // up to 912 positions (G 5, w 11) 342 -> 338 us, 272 units of up to 1088 (d 64, w 34) 67.9 -> 65.3 us, 384 of 8208 (G 5, w 128) 1390 ->
+    // 1380 us.  Not where the registers are full: 512 units of 4112 with the fused redundancy (REF 2) 659 -> 696 us, 80 units of 4288 with
+    // the separate one 356 -> 361 us.
+    constexpr bool FIRST_MAX = REF < 2 || (REF == 3 && RB > 1);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int *tbl = (int *)(smem + a.off_tbl), *dst = (int *)(smem + a.off_dst);
     Misc *misc = (Misc *)(smem + a.off_misc);
@@ -189,7 +194,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     // The sum of exp2(x - ref) is kept against a per-row reference `rm` that only moves when the sum leaves the
     // safe range (first subtile, or logits that jump by more than ~2^100): then the subtile is redone with the
     // proper maximum.  This keeps the common path free of the max reduction: fma, exp2, add per logit.
-    auto sweep1_body = [&](const char *buf, int j0, auto edge_tag) {
+    auto sweep1_body = [&](const char *buf, int j0, bool fresh, auto edge_tag) {   // fresh: a segment's first tile
         constexpr bool edge = decltype(edge_tag)::value;
 #pragma unroll
         for (int sub = 0; sub < KT / 32; sub++) {
@@ -213,6 +218,12 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
                         if (j > lim) acc[rb][i] = -INFINITY;
                     }
                 }
+                if (FIRST_MAX && sub == 0 && fresh) {        // the reference that the redo below would find
+                    float tm = acc[rb][0];
+#pragma unroll
+                    for (int i = 1; i < 16; i++) tm = fmaxf(tm, acc[rb][i]);
+                    rm[rb] = fmaxf(-1e30f, tm * c);
+                }
                 float sum = 0.f;
 #pragma unroll
                 for (int i = 0; i < 16; i++) sum += fexp2(fmaf(acc[rb][i], c, -rm[rb]));
@@ -233,9 +244,9 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             }
         }
     };
-    auto sweep1_tile = [&](const char *buf, int j0) {
-        if (j0 + KT > u.Tv - w) sweep1_body(buf, j0, std::true_type());
-        else sweep1_body(buf, j0, std::false_type());
+    auto sweep1_tile = [&](const char *buf, int j0, bool fresh) {
+        if (j0 + KT > u.Tv - w) sweep1_body(buf, j0, fresh, std::true_type());
+        else sweep1_body(buf, j0, fresh, std::false_type());
     };
     // end of a segment: the two half-waves hold the same row, different keys; then the segments in ascending order
     float *lsum = part;                                      // [NB*32] sums beside the references in lse (part: sweep 2 only)
@@ -276,12 +287,12 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
 #pragma unroll 1
     for (int it = t_lo; it < t_hi; it += 2) {
         if (it + 2 < t_hi) gload(it + 2, stB, ZP_NT1());
-        sweep1_tile(buf0, it * KT);
+        sweep1_tile(buf0, it * KT, it + seg_len == seg_end);
         if (it + 1 < t_hi) lstore(buf1, stA);
         __syncthreads();
         if (it + 1 >= t_hi) break;
         if (it + 3 < t_hi) gload(it + 3, stA, ZP_NT1());
-        sweep1_tile(buf1, (it + 1) * KT);
+        sweep1_tile(buf1, (it + 1) * KT, false);
         if (it + 2 < t_hi) lstore(buf0, stB);
         if (it + 2 == seg_end && seg_end < t_hi) {
             close_segment(sg++);
