@@ -12,9 +12,10 @@
 
 namespace zp {
 
-// A workgroup may use the whole 160 KB of LDS; the runtime wants to be told once per kernel.
-template <class K> static hipError_t allow_big_lds(K kernel) {
-    static hipError_t state = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+// A workgroup may use the whole 160 KB of LDS; the runtime is told once per kernel (all kernels here are of one type, so the
+// kernel itself is the template's parameter).
+template <auto Kernel> static hipError_t allow_big_lds() {
+    static hipError_t state = hipFuncSetAttribute((const void *)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     return state;
 }
 

@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(256) unit_generic(const Args a) {
 
 hipError_t launch_unit_generic(const Args &a, int units, hipStream_t s) {
     if (units <= 0) return hipSuccess;
-    hipError_t e = a.dtype == 0 ? allow_big_lds(unit_generic<0>) : allow_big_lds(unit_generic<1>);
+    hipError_t e = a.dtype == 0 ? allow_big_lds<unit_generic<0>>() : allow_big_lds<unit_generic<1>>();
     if (e != hipSuccess) return e;
     if (a.dtype == 0) hipLaunchKernelGGL(unit_generic<0>, dim3(units), dim3(256), a.lds_bytes, s, a);
     else hipLaunchKernelGGL(unit_generic<1>, dim3(units), dim3(256), a.lds_bytes, s, a);
@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(1024) unit_sliced(const Args a) {
 
 hipError_t launch_unit_sliced(const Args &a, int units, hipStream_t s) {
     if (units <= 0) return hipSuccess;
-    hipError_t e = allow_big_lds(unit_sliced);
+    hipError_t e = allow_big_lds<unit_sliced>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(unit_sliced, dim3(units * a.slices), dim3(1024), a.lds_bytes, s, a);
     return hipGetLastError();
@@ -139,8 +139,9 @@ static void pick_geometry(int NB, int *NW, int *RB) {
 // bf16 rows of 128 and 256 bytes have kernels of their own; every other row, and windows of more than 32 query blocks, runs
 // padded to the next of a few sizes.  Before, those shapes took one dot product per (query row, key) on the vector ALUs with
 // one key row per lane (uncoalesced 16-byte steps): fp32, d = 128, G = 4, w = 32, 128 units of 1040 positions 17.6 ms ->
-// 0.294 ms; bf16, d = 96, G = 3, w = 20, 72 units of up to 1248 positions 6.98 ms -> 0.154 ms.  A padded k step costs 1/16 of
-// a tile's products per 32 bytes, far less than the smallest gap between sizes would give back.
+// 0.294 ms; bf16, d = 96, G = 3, w = 20, 72 units of up to 1248 positions 6.98 ms -> 0.154 ms.  A padded k step of
+// 32 bytes costs its share of a tile's products, 1/4 of them at 128 bytes and 1/32 at 1024; every further size is another set of
+// kernels.
 bool mfma_path_available(const Args &a, MfmaGeo *g) {
     if (a.G < 1 || a.G > 16) return false;
     const int UL = 16 / a.G, NB = (a.w + 2 * UL - 1) / (2 * UL);

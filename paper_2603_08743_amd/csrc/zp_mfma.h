@@ -17,7 +17,7 @@ namespace zp {
 // waves per workgroup and two workgroups per CU put four waves on every SIMD, which overlaps the matrix-core and
 // vector-ALU phases of different waves and gives the row-moving phase sixteen waves per CU to issue memory operations
 // from (measured on the 8B-like shape: 15.0 ms per launch against 17.0 ms with four waves of two blocks each).
-// Rows above 256 bytes keep 16 more registers of query fragments per 64 bytes: half the waves.
+// Rows above 256 bytes keep 8 more registers of query fragments per 64 bytes, and as many again of tile loads: half the waves.
 #define ZP_WPE(NW, RB, ROWB) ((NW) == 8 && (RB) == 1 && (ROWB) <= 256 ? 4 : ((NW) >= 4 ? 2 : 1))
 
 // ------------------------------------------------------------------ matrix-core path
@@ -486,7 +486,7 @@ static hipError_t launch_one(const Args &a, int units, hipStream_t s) {
         if (a.phase == 1) return launch_one<DT, ROWB, PAD, RB, NW, GT, REF, MP, 1>(a, units, s);
         if (a.phase == 2) return launch_one<DT, ROWB, PAD, RB, NW, GT, REF, MP, 2>(a, units, s);
     }
-    hipError_t e = allow_big_lds(unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP, PH>);
+    hipError_t e = allow_big_lds<unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP, PH>>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((unit_mfma<DT, ROWB, PAD, RB, NW, GT, REF, MP, PH>), dim3(PH ? units * a.parts : units), dim3(NW * 64), a.lds_bytes, s, a);
     return hipGetLastError();

@@ -8,6 +8,7 @@
 #include <string>
 
 static std::string g_log;
+static std::string g_attributes;              // kernels that were given the large LDS limit, since the library was loaded
 static std::map<std::string, int> g_set;      // stub_set: device, stream_device, capturing, no_memory
 static std::map<const void *, std::string> &names() {   // filled while the library is loaded, before this file's own variables exist
     static std::map<const void *, std::string> m;
@@ -27,6 +28,7 @@ static void note(const char *fmt, ...) {
 
 extern "C" {
 const char *stub_log() { return g_log.c_str(); }
+const char *stub_attributes() { return g_attributes.c_str(); }
 void stub_clear() { g_log.clear(); }
 void stub_set(const char *what, int value) { g_set[what] = value; }
 
@@ -50,7 +52,7 @@ hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "stub"; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { *p = stub_blob; return hipSuccess; }
-hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute, int v) { note("attribute %s %d", names()[f].c_str(), v); return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute, int v) { g_attributes += names()[f] + " " + std::to_string(v) + "\n"; return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *c) {
     *c = g_set["capturing"] ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;

@@ -31,7 +31,7 @@ def lib(tmp_path_factory):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     h = ctypes.CDLL(so)
-    h.stub_log.restype = ctypes.c_char_p
+    h.stub_log.restype = h.stub_attributes.restype = ctypes.c_char_p
     h.zp_last_error.restype = ctypes.c_char_p
     h.zp_last_error.argtypes = [ctypes.c_void_p]
     h.zp_destroy.restype = None
@@ -179,3 +179,13 @@ def test_no_more_than_three_quarters_of_the_compute_units(lib):
     assert [len(c.launches("compress", units=u, w=4)) for u in (192, 193)] == [3, 1]
     assert [c.launches("select", units=u)[0].split()[1] for u in (192, 193)] == ["unit_sliced", "unit_generic"]
     assert [c.launches("compact", units=u)[0].split()[1] for u in (192, 193)] == ["unit_sliced", "unit_generic"]
+
+
+def test_every_kernel_is_given_the_large_lds_limit(lib):
+    c = Caller(lib)
+    c.launches("select", units=8)                                              # unit_sliced
+    c.launches("select", units=600)                                            # unit_generic<1>
+    c.launches("select", units=600, dtype="f32")                               # unit_generic<0>
+    told = lib.stub_attributes().decode().splitlines()
+    for kernel in ("unit_sliced", "unit_genericILi0E", "unit_genericILi1E"):
+        assert sum(kernel in l and l.endswith(" 163840") for l in told) == 1, (kernel, told)
