@@ -105,6 +105,10 @@ const char *zp_last_error(const zp_ctx *ctx); /* ctx may be NULL: text of the la
    event; under graph capture, without workspaces and in zp_compress_static every call is one launch. */
 size_t zp_scratch_bytes(const zp_pool *pool, const zp_batch *batch);
 
+/* Kernel launches of the last scoring, selecting or compacting call through ctx that passed its argument checks: 0 (nothing to
+   do), 1, or 2 (zp_score) and 3 (zp_compress) for a call of few units that is split.  For tests and traces. */
+int32_t zp_last_launches(const zp_ctx *ctx);
+
 /* Tuning / test switches.  ZP_OPT_SPLIT: -1 (default) and 0 are accepted and change nothing; 1 asked for a kernel in which
    several workgroups of a unit wait for each other, whose bounded wait expired intermittently on MI355X without a cause
    being established: it is not part of the library and the value returns ZP_EUNSUPPORTED.

@@ -22,7 +22,7 @@ ZP_OPT_SPLIT, ZP_OPT_SPIN_LIMIT, ZP_OPT_STREAMS, ZP_OPT_XCD_MAP = 1, 2, 3, 4
 
 EXPORTS = ("zp_create", "zp_destroy", "zp_last_error", "zp_scratch_bytes", "zp_score", "zp_select_topk", "zp_compact_kv",
            "zp_compress", "zp_sync_status", "zp_validate_batch", "zp_plan", "zp_set_option", "zp_decode_attention", "zp_score_ex",
-           "zp_compact_kv_ex", "zp_compress_ex", "zp_compress_static")
+           "zp_compact_kv_ex", "zp_compress_ex", "zp_compress_static", "zp_last_launches")
 
 
 class ZpError(RuntimeError):
@@ -243,6 +243,9 @@ class Context:
 
     def zp_set_option(self, option: int, value: int) -> None:
         self._check(self.lib.zp_set_option(self.h, ctypes.c_int32(option), ctypes.c_int32(value)))
+
+    def zp_last_launches(self) -> int:
+        return int(self.lib.zp_last_launches(self.h))
 
     def zp_sync_status(self) -> None:
         self._check(self.lib.zp_sync_status(self.h, _stream()))

@@ -4,6 +4,7 @@
 #include "../../include/zp.h"
 #include "zp_kernels.h"
 
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -22,6 +23,7 @@ struct zp_ctx {
     int *h_status;   // pinned mirror
     int xcd_map;     // workgroup -> unit map: 1 contiguous ranges per XCD, 0 identity
     int n_cu;        // compute units: every kernel here fits at least one workgroup per CU
+    std::atomic<int> launches;   // kernel launches of the last call (zp_last_launches)
     char err[512];
     // Workspaces of the calls that take several launches (partial sums of sweep 1, scores between the launches).  A call takes the
     // one its stream used last, else the next in turn, waits on the device for that one's last call and records an event after
@@ -325,9 +327,13 @@ static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, co
     return e != hipSuccess ? e : er;
 }
 
+extern "C" int32_t zp_last_launches(const zp_ctx *ctx) { return ctx ? ctx->launches.load() : 0; }
+
 static zp_status launch(zp_ctx *ctx, const char *who, zp::Args &a, Path path, const zp::MfmaGeo &geo, void *stream) {
     const int units = a.B * a.L_slab * a.h_kv;
+    ctx->launches = units > 0;
     if (const int parts = split_parts(ctx, a, path, geo, (hipStream_t)stream)) {
+        ctx->launches = (a.stages & zp::STAGE_SELECT) ? 3 : 2;
         const hipError_t e = launch_split(ctx, a, parts, units, geo, (hipStream_t)stream);
         if (e != hipSuccess) return fail(ctx, ZP_EHIP, "%s: kernel launch failed: %s", who, hipGetErrorString(e));
         return ZP_OK;
@@ -464,7 +470,7 @@ extern "C" zp_status zp_compress_static(const zp_pool *pool, const zp_batch *bat
         }
     }
     zp_ctx tmp;                                               // host-side only: carries defaults and the error text
-    tmp.device = dev; tmp.d_status = words; tmp.h_status = nullptr; tmp.xcd_map = 1; tmp.n_cu = 0; tmp.err[0] = 0;
+    tmp.device = dev; tmp.d_status = words; tmp.h_status = nullptr; tmp.xcd_map = 1; tmp.n_cu = 0; tmp.launches = 0; tmp.err[0] = 0;
     for (auto &w : tmp.slot) w = {};
     tmp.next_slot = 0;
     zp::Args a; Path path; zp::MfmaGeo geo;
