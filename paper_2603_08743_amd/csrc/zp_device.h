@@ -607,14 +607,15 @@ __device__ inline void redundancy_mfma(const Args &a, const Unit &u, const int *
 // row zeroed in the column (-1: none) and its value.
 // Row fragments come from L2 (the unit's keys have just been swept), with few waves (FEW) those of the next tile requested
 // before the current tile is worked on.  Before, one thread per key took b dot products one element at a time: 345 ms per launch for 1152 units
-// of 2304 positions in blocks of 256 (d 128, bf16), now 1.71 ms.  Eight waves have 128 registers each and hold the column
+// of 2304 positions in blocks of 256 (d 128, bf16), now 1.71 ms.  Waves of 128 registers (TIGHT) hold the column
 // group only, rows of 192 and 256 bytes come piece by piece (512 units of 4112 positions, d 128, w 64: blocks of 64 1065 -> 1007 us,
-// of 256 1540 -> 1522 us against both held and 21 registers spilled).
-template <int ROWB, int DT, bool PAD, bool FEW>
+// of 256 1540 -> 1522 us against both held and 21 registers spilled; with 256 registers holding both is the faster way: 80 units of 3144
+// in blocks of 24, w 69, 372 against 403 us).
+template <int ROWB, int DT, bool PAD, bool FEW, bool TIGHT>
 __device__ inline void redundancy_blocks(const Args &a, const Unit &u, const int *tbl, float *rs, float *inv, int *zr, float *zv) {
     constexpr int KK = ROWB / 32;
     constexpr bool HOLD = ROWB <= 256;                           // a column group's fragments fit the registers ...
-    constexpr bool HOLD_ROWS = HOLD && (FEW || ROWB <= 128);     // ... beside those of a row group (two with FEW)
+    constexpr bool HOLD_ROWS = HOLD && (!TIGHT || ROWB <= 128);  // ... beside those of a row group (two with FEW)
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6, l32 = lane & 31, hf = lane >> 5;
     const int b = a.b, stale_hi = (u.N - 1) * b;
     const float inv_len = 1.0f / (float)u.Tv;
@@ -850,7 +851,7 @@ __device__ __forceinline__ void block_row_sums(const Args &a, const Unit &u, con
 // ROWB > 0: called from the matrix-core kernel for rows of up to ROWB bytes; ROWB = 0: generic kernel.  Element type DT.
 // REF 1: global score and pooling; REF 2: a launch whose similarity tiles came from sweep 2 (EX_RED_FUSED); REF 3: any other
 // with redundancy.
-template <int ROWB, int DT, bool PAD, int REF, int NW>
+template <int ROWB, int DT, bool PAD, int REF, int NW, bool TIGHT>
 __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, const int *tbl, Misc *misc) {
     const int tid = threadIdx.x, nt = blockDim.x;
     float *S = (float *)(smem + a.off_S);
@@ -897,7 +898,7 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
         } else {
             float *inv = tmp + a.T_max, *zv = tmp + 3 * (size_t)a.T_max;
             int *zr = (int *)(tmp + 2 * (size_t)a.T_max);
-            if constexpr (ROWB > 0) redundancy_blocks<ROWB, DT, PAD, NW <= 4>(a, u, tbl, tmp, inv, zr, zv);
+            if constexpr (ROWB > 0) redundancy_blocks<ROWB, DT, PAD, NW <= 4, TIGHT>(a, u, tbl, tmp, inv, zr, zv);
             else redundancy_valu<DT>(a, u, tbl, tmp, inv, zr, zv);
         }
         // R = softmax over the live sequence of (row sum / Tv) / tau, in base 2
@@ -919,8 +920,9 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
 
 // Everything after S sits in LDS: refinements, optional score output, selection, optional list output, compaction.
 // REF: score refinements are compiled in (a launch without them runs a kernel that does not carry their code).
+// TIGHT: four waves per SIMD, 128 registers each.
 // SLICED: this workgroup is one of a.slices that move the unit's rows; the first of them writes the other outputs.
-template <int ROWB, int DT, bool PAD, int REF, int NW, bool SLICED = false>
+template <int ROWB, int DT, bool PAD, int REF, int NW, bool TIGHT, bool SLICED = false>
 __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const int *tbl, const int *dst, Misc *misc, int slice = 0) {
     const int tid = threadIdx.x, nt = blockDim.x;
     float *S = (float *)(smem + a.off_S);
@@ -931,7 +933,7 @@ __device__ inline void unit_tail(const Args &a, const Unit &u, char *smem, const
         __syncthreads();
     }
     if constexpr (REF != 0) {
-        if ((a.stages & STAGE_SCORE) && (a.ex & (EX_GLOBAL | EX_POOL | EX_RED))) refine_unit<ROWB, DT, PAD, REF, NW>(a, u, smem, tbl, misc);
+        if ((a.stages & STAGE_SCORE) && (a.ex & (EX_GLOBAL | EX_POOL | EX_RED))) refine_unit<ROWB, DT, PAD, REF, NW, TIGHT>(a, u, smem, tbl, misc);
     }
     if (a.scores_out && (!SLICED || slice == 0)) {
         float *o = a.scores_out + (size_t)u.unit * a.T_max;

@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(256) unit_generic(const Args a) {
     Unit u;
     if (!unit_setup(a, unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map), u, tbl, dst, misc)) return;
     if (a.stages & STAGE_SCORE) score_generic<DT>(a, u, smem, tbl);
-    unit_tail<0, DT, false, 3, 4>(a, u, smem, tbl, dst, misc);
+    unit_tail<0, DT, false, 3, 4, false>(a, u, smem, tbl, dst, misc);
 }
 
 hipError_t launch_unit_generic(const Args &a, int units, hipStream_t s) {
@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(1024) unit_sliced(const Args a) {
     const int v = unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map);
     Unit u;
     if (!unit_setup<true>(a, v / a.slices, u, tbl, dst, misc)) return;
-    unit_tail<0, 1, false, 0, 16, true>(a, u, smem, tbl, dst, misc, v % a.slices);
+    unit_tail<0, 1, false, 0, 16, false, true>(a, u, smem, tbl, dst, misc, v % a.slices);
 }
 
 hipError_t launch_unit_sliced(const Args &a, int units, hipStream_t s) {

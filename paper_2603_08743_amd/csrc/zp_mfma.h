@@ -477,7 +477,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         return;
     }
     }
-    unit_tail<ROWB, DT, PAD, REF, NW>(a, u, smem, tbl, dst, misc);
+    unit_tail<ROWB, DT, PAD, REF, NW, ZP_WPE(NW, RB, ROWB) == 4>(a, u, smem, tbl, dst, misc);
 }
 
 template <int DT, int ROWB, bool PAD, int RB, int NW, int GT, int REF, bool MP, int PH = 0>
