@@ -248,12 +248,22 @@ static size_t workspace_bytes(const zp::Args &a, const zp::MfmaGeo &geo, long lo
     return seg_bytes(geo, units) + (size_t)units * sizeof(int2) + (size_t)units * a.T_max * 4;
 }
 
-// len_out inside one of the arrays that every launch of a call reads again (valid_len and keep are read once, see unit_scalars)
-static bool overlaps_tables(const zp::Args &a, long long units) {
+static bool len_out_meets(const zp::Args &a, long long units, const int *p, long long n) {
     const uintptr_t lo = (uintptr_t)a.len_out, hi = lo + (uintptr_t)units * 4;
-    auto meets = [&](const int *p, long long n) { return a.len_out && p && lo < (uintptr_t)p + (uintptr_t)n * 4 && (uintptr_t)p < hi; };
-    return meets(a.num_blocks, a.B) || meets(a.q_slot, a.B) || meets(a.block_table, (long long)a.B * a.max_blocks) ||
-           meets(a.dst_table, (long long)a.B * (a.N_max - 1));
+    return a.len_out && p && lo < (uintptr_t)p + (uintptr_t)n * 4 && (uintptr_t)p < hi;
+}
+
+// len_out inside one of the arrays that every launch of a call reads again
+static bool overlaps_tables(const zp::Args &a, long long units) {
+    return len_out_meets(a, units, a.num_blocks, a.B) || len_out_meets(a, units, a.q_slot, a.B) ||
+           len_out_meets(a, units, a.block_table, (long long)a.B * a.max_blocks) || len_out_meets(a, units, a.dst_table, (long long)a.B * (a.N_max - 1));
+}
+
+// len_out inside valid_len or keep: the row-moving launch, where one workgroup of a unit writes it and others read them, takes both
+// from the workspace (see unit_scalars; always taking them there costs 1 us of 33 on 32 units of 1296 positions)
+static bool overlaps_scalars(const zp::Args &a, long long units) {
+    const long long n = (long long)a.B * a.L * a.h_kv;
+    return len_out_meets(a, units, a.valid_len, n) || len_out_meets(a, units, a.keep, n);
 }
 
 // Workgroups per unit of the two scoring launches (0: one launch does everything).
@@ -308,7 +318,7 @@ static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, co
     m.stages = zp::STAGE_SCORE;
     m.keep_idx_out = nullptr;
     m.seg = (float2 *)w.mem;
-    m.unit_out = whole ? scalars : nullptr;
+    m.unit_out = whole && overlaps_scalars(a, units) ? scalars : nullptr;
     m.scores_out = scores;
     m.parts = parts;
     w.used = true;
@@ -318,7 +328,7 @@ static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, co
         a.stages = zp::STAGE_LOAD_SCORES | zp::STAGE_SELECT | zp::STAGE_COMPACT | zp::STAGE_CHECK_SLOT;
         a.scores_in = scores;
         a.scores_in_stride = a.T_max;
-        a.unit_in = scalars;
+        a.unit_in = m.unit_out;
         a.lds_bytes = a.off_union + align16(a.budget * 4);
         pick_slices(ctx, &a, units);
         e = zp::launch_unit_sliced(a, units, s);

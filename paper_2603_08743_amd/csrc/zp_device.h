@@ -1,6 +1,6 @@
 // Device-side building blocks shared by the unit kernels: per-unit metadata checks, the
 // order-preserving score key, radix top-k with the lower-position tie-break, and the
-// alias-safe row mover.  One workgroup processes one unit = (request, layer, kv head).
+// alias-safe row mover.  A unit is one (request, layer, kv head).
 #pragma once
 #include "zp_kernels.h"
 

@@ -1,9 +1,11 @@
-// Unit kernels of libzp: one workgroup per (request, layer, kv head).
+// Unit kernels of libzp.  A unit is one (request, layer, kv head); one workgroup takes a whole unit, or several share it over several
+// launches where units are few (split_pays in zp_api.hip).
 //
 //  * unit_mfma: the (G*w) x T logits are a dense contraction over d, so they run on the matrix cores
 //    (v_mfma_f32_32x32x16_bf16, v_mfma_f32_32x32x2_f32) from LDS-staged key tiles.
 //  * unit_generic: scoring on the vector ALUs for what does not fit there (more than 16 query heads per kv head,
-//    sequences whose scores leave no room for two key tiles in LDS), and the staged select-only / compact-only passes.
+//    sequences whose scores leave no room for two key tiles in LDS), and the staged select-only / compact-only passes of many units.
+//  * unit_sliced: selection and row moving of few units, the rows cut into slices.
 //
 // Scores follow the appendix "Paged Attention Score": softmax over positions per window
 // query, max over the query heads of the group, mean over the window.  The max over heads

@@ -18,6 +18,9 @@ namespace zp {
 // vector-ALU phases of different waves and gives the row-moving phase sixteen waves per CU to issue memory operations
 // from (measured on the 8B-like shape: 15.0 ms per launch against 17.0 ms with four waves of two blocks each).
 // Rows above 256 bytes keep 8 more registers of query fragments per 64 bytes, and as many again of tile loads: half the waves.
+// Padded rows of 192 and 256 bytes with eight waves and 1024-byte rows with four spill at these targets (29 to 54, and 83 to 127
+// registers).  With half the waves and no spills 128 units of 1040 positions are faster (d 96, w 64 95 -> 89 us; fp32 d 256, w 32 465 ->
+// 426), 512 units slower (180 -> 207; 1040 -> 1162; refined bf16 d 512 679 -> 845): the second workgroup per compute unit is worth more.
 #define ZP_WPE(NW, RB, ROWB) ((NW) == 8 && (RB) == 1 && (ROWB) <= 256 ? 4 : ((NW) >= 4 ? 2 : 1))
 
 // ------------------------------------------------------------------ matrix-core path

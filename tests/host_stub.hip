@@ -72,8 +72,8 @@ hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipSt
     const std::string &name = names()[f];
     if (name.find("unit_") == std::string::npos) { note("launch %s", name.c_str()); return hipSuccess; }
     const zp::Args &a = *(const zp::Args *)args[0];
-    note("launch %s units %d stages %d slices %d slice_bytes %d lds %d", name.find("sliced") != std::string::npos ? "unit_sliced" : "unit_generic",
-         a.B * a.L_slab * a.h_kv, a.stages, a.slices, a.slice_bytes, a.lds_bytes);
+    note("launch %s units %d stages %d slices %d slice_bytes %d lds %d fixed %d", name.find("sliced") != std::string::npos ? "unit_sliced" : "unit_generic",
+         a.B * a.L_slab * a.h_kv, a.stages, a.slices, a.slice_bytes, a.lds_bytes, a.unit_in != nullptr);
     return hipSuccess;
 }
 }  // extern "C"

@@ -109,11 +109,14 @@ def test_calls_on_another_gpu_leave_the_workspaces_alone(lib, stream):
         assert len(log) == 1 and "phase 0" in log[0], log
 
 
-@pytest.mark.parametrize("name,split", [("vl", True), ("keep", True), ("nb", False), ("slot", False), ("tbl", False)])
-def test_len_out_inside_the_batch_arrays(lib, name, split):
-    """valid_len and keep are read once per call; a table that every launch reads again keeps the call to one launch."""
-    log = Caller(lib).launches("compress", at={"len": ADDRESS[name]})
+@pytest.mark.parametrize("name,split", [("len", True), ("vl", True), ("keep", True), ("nb", False), ("slot", False), ("tbl", False)])
+@pytest.mark.parametrize("offset", [0, 4 * 63, -4 * 63])
+def test_len_out_inside_the_batch_arrays(lib, name, split, offset):
+    """valid_len and keep are then read once per call; a table that every launch reads again keeps the call to one launch."""
+    log = Caller(lib).launches("compress", at={"len": ADDRESS[name] + offset})
     assert len(log) == (3 if split else 1)
+    if split:
+        assert log[2].endswith("fixed %d" % (name != "len"))
 
 
 def test_workspaces_by_stream(lib):
