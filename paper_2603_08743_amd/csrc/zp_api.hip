@@ -220,26 +220,35 @@ static bool few_units(const zp_ctx *ctx, long long units) { return units <= ctx-
 //                                     768 positions  55: 48      512  39: 46
 //                         96         1040            80: 75      768  60: 63
 //                        128         2064           151:135     1040  84: 92
-//                        160 or 192  up to 8208 never worth it (4112: 298:314, 316:344)
+//                        160 or 192  up to 8208 never worth it (4112: 298:314, 316:344), but with live lengths from a quarter to
+//                                    the whole of the positions, where the longest unit holds up the one launch, 160  4112 257:222,
+//                                    2384 156:156;  192  4112 262:253  2384 159:176
 //   four (w 32):   128 or fewer 512  52: 51;   160  1040 108: 97  768 78: 82;   192  1040 111:108  768 82: 91
 //   two (w 16):    192  768  92: 82   512 63: 67;    one (w 4): 192  512  96: 68
 //   several blocks per wave (w 112), four workgroups per unit that fill a compute unit each:
 //                   64   512  53: 47;    96  1040 105: 99   768 79: 82;   128  1040 109:107;   160 4112 381:408
 //   two staged scoring launches against one, the row moving being sliced either way, need 8/5 of the positions:
 //                  128 of eight waves  2064 211:209  1040 118:131;   192 of four  2064 228:219  1040 125:131
-// Rows of 128 bytes (d 64) have less to share out, fp32 and other long rows more (eight waves, fp32, 128 units: 512 183:172).
-static bool split_pays(int n_cu, long long units, int T, const zp::MfmaGeo &geo, bool f32, bool whole) {
+// Rows of 128 bytes (d 64) have less to share out; fp32, other long rows and padded rows more (eight waves, 128 units: fp32 512
+// 183:172; d 96 1040 96:86, staged 848 74:71).
+static bool split_pays(int n_cu, long long units, int T, const zp::MfmaGeo &geo, bool f32, bool whole, bool ragged) {
     const long long u = units * 256 / n_cu;                    // the same share of 256 compute units
     if (T < 512) return false;
-    if (geo.RB > 1 && u <= 64) return T >= (geo.rowb <= 128 ? 768 : 512);
+    if (geo.RB > 1 && u <= 64) return T >= (geo.rowb <= 128 && geo.RB == 2 ? 768 : 512);
     const bool heavy = geo.RB > 2 || geo.rowb > 256;
     if (u > 128) {                                             // two rounds of row-moving workgroups
-        if (geo.NW == 8) return heavy ? T >= 16 * u : !whole && T >= 24 * u;
+        if (geo.NW == 8) {
+            if (heavy) return T >= 16 * u;
+            if (geo.pad) return (ragged || !whole) && T >= 12 * u;
+            return whole ? ragged && T >= 18 * u : T >= 24 * u;
+        }
         if (geo.NW > 1 && geo.rowb <= 512 && T < 768) return false;
     }
-    const long long need = u * geo.NW * (whole ? 5 : 8) / 4 * (f32 ? 5 : heavy ? 8 : 10) / 10;
+    int eighths = whole ? 10 : 16;                             // positions per wave of one launch
+    if (geo.pad) eighths = f32 && whole ? 5 : 8;
+    else if (geo.RB > 1) eighths = whole ? (geo.RB > 2 ? 8 : 10) : 12;
     const bool early = heavy || geo.NW <= 2 || (geo.NW == 4 && geo.rowb > 128 && whole);
-    return T >= need && (early || T >= 640);
+    return T >= u * geo.NW * eighths / 8 && T >= (early ? 512 : geo.NW == 8 && geo.rowb <= 128 ? 768 : 640);
 }
 
 // Workspace of a call: partial sums of sweep 1, the units' scalars, the scores.
@@ -270,7 +279,7 @@ static bool overlaps_scalars(const zp::Args &a, long long units) {
 static int split_parts(const zp_ctx *ctx, const zp::Args &a, Path path, const zp::MfmaGeo &geo, hipStream_t s) {
     const long long units = (long long)a.B * a.L_slab * a.h_kv;
     if (path != PATH_MFMA || geo.NP != 1 || a.ex || !ctx->slot[0].mem || units <= 0 || !few_units(ctx, units) ||
-        !split_pays(ctx->n_cu, units, a.T_max, geo, a.dtype == 0, (a.stages & zp::STAGE_SELECT) != 0))
+        !split_pays(ctx->n_cu, units, a.T_max, geo, a.dtype == 0, (a.stages & zp::STAGE_SELECT) != 0, a.valid_len != nullptr))
         return 0;
     if (workspace_bytes(a, geo, units) > kSlotBytes || overlaps_tables(a, units)) return 0;
     int dev = -1;                                              // workspaces and events belong to the context's GPU

@@ -145,7 +145,8 @@ def test_row_moving_workgroups_run_at_once(lib, units, d, dtype):
         assert slices == (4 if units <= 64 else 2)
 
 
-# one launch against several, microseconds measured on 256 compute units (d 128, G 4, bf16 unless stated): which of the two is taken
+# one launch against several, microseconds measured on 256 compute units (d 128, G 4, bf16 unless stated): which of the two is taken.
+# RAGGED: with live lengths from a quarter to the whole of the positions (valid_len given); the others all live
 MEASURED = [
     # call, shape, units, positions, one launch, several
     ("compress", dict(w=64), 8, 768, 43, 34), ("compress", dict(w=64), 8, 512, 31, 33), ("compress", dict(w=64), 64, 768, 55, 48),
@@ -167,14 +168,28 @@ MEASURED = [
     ("score", dict(w=64), 160, 2064, 220, 232), ("score", dict(w=64), 160, 4112, 417, 400), ("score", dict(w=32), 192, 1040, 125, 131),
     ("score", dict(w=32), 192, 2064, 228, 219), ("score", dict(w=32), 96, 512, 57, 64), ("score", dict(w=16), 192, 512, 71, 77),
     ("score", dict(w=16), 192, 768, 101, 96), ("score", dict(w=112), 64, 512, 70, 66), ("score", dict(w=112), 96, 1040, 136, 139),
+    ("compress", dict(w=64, d=96), 128, 1040, 96, 86), ("compress", dict(w=64, d=96), 192, 2064, 191, 213), ("score", dict(w=64, d=96), 64, 848, 67, 53),
+    ("score", dict(w=64, d=96), 160, 3168, 240, 204), ("score", dict(w=24, d=96), 192, 1088, 97, 93), ("score", dict(w=121, d=64, G=5, b=32), 64, 544, 55, 47),
+    ("score", dict(w=121, d=64, G=5, b=32), 128, 544, 58, 73), ("score", dict(w=112), 96, 1376, 114, 102),
+]
+RAGGED = [
+    (dict(w=64), 160, 4112, 257, 222), (dict(w=64), 160, 1040, 76, 96), (dict(w=64), 192, 2384, 159, 176), (dict(w=64), 192, 4112, 262, 253),
+    (dict(w=64), 96, 1040, 72, 66), (dict(w=64, d=80), 160, 2384, 180, 158), (dict(w=64, d=96), 192, 2384, 189, 179), (dict(w=64, d=96), 160, 1040, 90, 95),
+    (dict(w=32), 160, 640, 60, 68), (dict(w=32), 192, 1040, 97, 89), (dict(w=112), 160, 4112, 333, 295), (dict(w=112), 192, 1040, 101, 137),
+    (dict(w=64, d=64), 64, 640, 34, 37), (dict(w=64, d=64), 192, 4112, 174, 163),
 ]
 
 
 @pytest.mark.parametrize("call,shape,units,T,one,several", MEASURED)
 def test_the_faster_way_is_taken_on_both_sides_of_the_line(lib, call, shape, units, T, one, several):
     b = shape.get("b", 16)
-    n = len(Caller(lib).launches(call, units=units, T=T // b * b, **shape))
+    n = len(Caller(lib).launches(call, units=units, T=T // b * b, at={"vl": None}, **shape))
     assert n == (1 if one < several else 3 if call == "compress" else 2)
+
+
+@pytest.mark.parametrize("shape,units,T,one,several", RAGGED)
+def test_the_faster_way_is_taken_with_live_lengths_of_every_size(lib, shape, units, T, one, several):
+    assert len(Caller(lib).launches("compress", units=units, T=T, **shape)) == (1 if one < several else 3)
 
 
 def test_no_more_than_three_quarters_of_the_compute_units(lib):
