@@ -259,7 +259,10 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         m = mm;
     };
     auto close_segment = [&](int sg) {
-        asm volatile("" ::: "memory");                       // keeps the addresses below out of the tile loop: 12 spilled registers with REF 2, 26 without
+        // With eight waves the addresses below stay out of the tile loop (12 spilled registers with REF 2, 26 without).  Fewer waves have
+        // the registers, and there the barrier makes the loop wait for its loads: 512 units of 4112 positions with the fused redundancy
+        // (one wave, G 4, w 8) 1193 against 1052 us, with the separate one (d 64, two waves, blocks of 32) 176 against 170 us at 528.
+        if (NW == 8) asm volatile("" ::: "memory");
 #pragma unroll
         for (int rb = 0; rb < RB; rb++) {
             const float mo = __shfl_xor(rm[rb], 32), lo = __shfl_xor(rl[rb], 32);
