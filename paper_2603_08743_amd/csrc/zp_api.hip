@@ -346,6 +346,21 @@ static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, co
     return e != hipSuccess ? e : er;
 }
 
+// Costliest units first (unit_by_cost) where live lengths differ from head to head and some units have to wait for others to end: up to two rounds of
+// workgroups, four where a wave holds several query blocks.  With more rounds the short units of the last one even out by themselves,
+// and the order costs more than it gives: the kv heads of one (request, layer), which read the same blocks, then run far apart, which
+// only launches bound by the scoring arithmetic do not mind.  Measured, in order of number against by cost in us (d 128, bf16; live
+// lengths from a quarter of the positions on): several blocks per wave 384 units (1.5 rounds) 1386:972, 768 (3) 1109:923;
+// one block, live lengths 640 units 479:425, with all three refinements 768 594:506, four waves 1536 (2) 700:620, but
+// 1280 units (2.5) 940:965, 2048 (4) 1165:1224.  Where only the keep counts differ, scoring is alike and little is left to even out:
+// 768 units 879:870, f32 637:623, but 672 of seven heads 374:394; requests of different lengths with all heads alike: 1280 units 883:964.
+static bool order_by_cost(const zp_ctx *ctx, const zp::Args &a, const zp::MfmaGeo &geo, long long units) {
+    if (!a.valid_len || a.T_max < 1024 || overlaps_scalars(a, units) || overlaps_tables(a, units)) return false;
+    const int waves = geo.RB == 1 && geo.rowb <= 256 ? 16 : 8, by_regs = waves / geo.NW, by_lds = kLdsLimit / a.lds_bytes;
+    const long long at_once = (long long)ctx->n_cu * (by_regs < by_lds ? by_regs : by_lds);
+    return units > at_once && units <= (geo.RB > 1 ? 4 : 2) * at_once;
+}
+
 extern "C" int32_t zp_last_launches(const zp_ctx *ctx) { return ctx ? ctx->launches.load() : 0; }
 
 static zp_status launch(zp_ctx *ctx, const char *who, zp::Args &a, Path path, const zp::MfmaGeo &geo, void *stream) {
@@ -364,6 +379,7 @@ static zp_status launch(zp_ctx *ctx, const char *who, zp::Args &a, Path path, co
         if (e != hipSuccess) return fail(ctx, ZP_EHIP, "%s: kernel launch failed: %s", who, hipGetErrorString(e));
         return ZP_OK;
     }
+    a.by_cost = path == PATH_MFMA && order_by_cost(ctx, a, geo, units);
     hipError_t e = path == PATH_MFMA ? zp::launch_unit_mfma(a, units, geo, (hipStream_t)stream)
                                      : zp::launch_unit_generic(a, units, (hipStream_t)stream);
     if (e != hipSuccess) return fail(ctx, ZP_EHIP, "%s: kernel launch failed: %s", who, hipGetErrorString(e));

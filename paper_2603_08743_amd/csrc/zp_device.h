@@ -79,6 +79,64 @@ __device__ __forceinline__ int unit_of_block(int bid, int n, int mode) {
     return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
+__device__ __forceinline__ unsigned wave_incl_scan(unsigned x, int lane) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        unsigned y = __shfl_up(x, off);
+        if (lane >= off) x += y;
+    }
+    return x;
+}
+
+// The unit that a workgroup takes where units differ in length and there are more of them than run at once: the workgroups, which the
+// hardware starts in order, take the costliest units first, so that no long unit starts when the others are nearly done.  Costs
+// fall into 256 classes, units of a class are taken in order of their number.  A unit's cost: its query blocks times its live
+// entries (scoring) and eight times its kept rows (moving).  Every workgroup derives the order from arrays that nothing writes during the launch.
+// 384 units of 2064 to 8208 entries (G 5, w 128, one workgroup per compute unit): 1386 us in order of their number, 972 us by cost.
+__device__ inline int unit_by_cost(const Args &a, int rank, int n, Misc *misc) {
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
+    const unsigned blocks = (unsigned)((a.G * a.w + 31) >> 5);
+    const float scale = 256.0f / (float)(blocks * (unsigned)a.T_max + 8u * (unsigned)a.budget + 1u);
+    auto cls = [&](int u) {
+        const int h = u % a.h_kv, ls = (u / a.h_kv) % a.L_slab, nq = u / (a.h_kv * a.L_slab), idx = (nq * a.L + a.layer0 + ls) * a.h_kv + h;
+        unsigned live = a.valid_len ? (unsigned)(a.valid_len[idx] + a.b) : (unsigned)a.num_blocks[nq] * (unsigned)a.b;
+        unsigned k = a.keep ? (unsigned)a.keep[idx] : (unsigned)a.budget;
+        live = live < (unsigned)a.T_max ? live : (unsigned)a.T_max;      // bad values end in some class, the unit is refused later
+        k = k < (unsigned)a.budget ? k : (unsigned)a.budget;
+        const int c = (int)((float)(blocks * live + 8u * k) * scale);
+        return 255 - (c < 255 ? c : 255);
+    };
+    for (int i = tid; i < 256; i += nt) misc->hist[i] = 0;
+    __syncthreads();
+    for (int u = tid; u < n; u += nt) atomicAdd(&misc->hist[cls(u)], 1);
+    __syncthreads();
+    if (tid < 64) {
+        int c[4], sum = 0;
+        for (int i = 0; i < 4; i++) sum += c[i] = misc->hist[4 * lane + i];
+        int before = (int)wave_incl_scan((unsigned)sum, lane) - sum;
+        if (before <= rank && rank < before + sum) {             // one lane
+            int i = 0;
+            while (rank >= before + c[i]) before += c[i++];
+            misc->sel_digit = 4 * lane + i;
+            misc->sel_gt = rank - before;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        const int want = misc->sel_digit;
+        int left = misc->sel_gt;
+        for (int u0 = 0; u0 < n; u0 += 64) {
+            const unsigned long long m = __ballot(u0 + lane < n && cls(u0 + lane < n ? u0 + lane : 0) == want);
+            const int here = __popcll(m);
+            if (left < here) {
+                if ((m >> lane & 1) && __popcll(m & ((1ull << lane) - 1)) == left) misc->pad = u0 + lane;
+                break;
+            }
+            left -= here;
+        }
+    }
+    __syncthreads();
+    return misc->pad;
+}
+
 // Decode the unit and check its scalar metadata (identical for every thread and every workgroup
 // that looks at the unit).  Returns 0 or the reason the unit must be skipped.
 // FIXED: several workgroups of a unit come through here in the launch that writes len_out, and a caller may pass valid_len or keep
@@ -160,15 +218,6 @@ __device__ __forceinline__ unsigned score_key(float f) {
 }
 #define ZP_KEY_NEG_INF 0x007fffffu
 #define ZP_KEY_POS_INF 0xff800000u
-
-__device__ __forceinline__ unsigned wave_incl_scan(unsigned x, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        unsigned y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
-    return x;
-}
 
 // Selection (Method, compression pipeline): window +inf, stale -inf, keep the k largest, ties to the
 // lower position.  keys: LDS, holds fp32 scores on entry, destroyed.  list: LDS, receives the k kept

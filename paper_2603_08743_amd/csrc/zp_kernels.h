@@ -45,6 +45,7 @@ struct Args {
     float scale_log2;                          // log2(e) / sqrt(d)
     int stages;
     int xcd_map;                               // 1: contiguous unit ranges per XCD (see unit_of_block)
+    int by_cost;                               // 1: costliest units first (see unit_by_cost)
     // staged inputs / outputs (device pointers, any may be null depending on stages)
     const float *scores_in; int scores_in_stride;
     float *scores_out;                         // [units][T_max]

@@ -73,6 +73,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     Unit u;
     int uid = unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map), part_no = 0;
     if (PH) { part_no = uid % a.parts; uid /= a.parts; }
+    else if (a.by_cost) uid = unit_by_cost(a, (int)blockIdx.x, (int)gridDim.x, misc);
     const bool usable = unit_setup(a, uid, u, tbl, dst, misc);
     if (PH == 2 && part_no == 0 && threadIdx.x == 0 && a.unit_out) a.unit_out[uid] = usable ? make_int2(u.vl, u.k) : make_int2(-1, -1);
     if (!usable) return;
