@@ -92,6 +92,7 @@ extern "C" void zp_destroy(zp_ctx *ctx) {
 
 static int align16(int x) { return (x + 15) & ~15; }
 static const int kLdsLimit = 160 * 1024;
+static const int kMiscBytes = align16((int)sizeof(int) * (256 + 16 + 4));
 
 enum Path { PATH_GENERIC, PATH_MFMA };
 
@@ -180,12 +181,11 @@ static zp_status prepare(zp_ctx *ctx, const char *who, const zp_pool *p, const z
         const size_t red_bytes = mf && 32 % p->b == 0 ? (size_t)geo->NW * 96 * 4 : (size_t)a->T_max * 12;
         const size_t refine_bytes = ((a->ex & (zp::EX_POOL | zp::EX_RED)) ? (size_t)a->T_max * 4 : 0) + ((a->ex & zp::EX_RED) ? red_bytes : 0);
         const size_t list_bytes = (size_t)a->budget * 4;
-        const int misc_bytes = align16((int)sizeof(int) * (256 + 16 + 4));
         a->off_S = 0;
         a->off_tbl = align16(a->T_max * 4);
         a->off_dst = a->off_tbl + align16(a->max_blocks * 4);
         a->off_misc = a->off_dst + align16((a->N_max - 1) * 4);
-        a->off_union = a->off_misc + misc_bytes;
+        a->off_union = a->off_misc + kMiscBytes;
         size_t union_bytes = score_bytes > list_bytes ? score_bytes : list_bytes;
         if (refine_bytes > union_bytes) union_bytes = refine_bytes;
         a->off_G = a->off_union + align16((int)union_bytes);
@@ -330,6 +330,10 @@ static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, co
     m.unit_out = whole && overlaps_scalars(a, units) ? scalars : nullptr;
     m.scores_out = scores;
     m.parts = parts;
+    m.off_tbl = 0;                                            // the two scoring launches keep no scores and no targets on chip
+    m.off_misc = align16(a.max_blocks * 4);
+    m.off_union = m.off_misc + kMiscBytes;
+    m.lds_bytes = align16(m.off_union + (int)zp::mfma_union_bytes(geo));
     w.used = true;
     w.stream = (void *)s;
     for (m.phase = 1; m.phase <= 2 && e == hipSuccess; m.phase++) e = zp::launch_unit_mfma(m, units, geo, s);

@@ -153,57 +153,52 @@ __device__ inline int unit_scalars(const Args &a, int unit, Unit &u) {
     u.h = unit % a.h_kv;
     u.ls = (unit / a.h_kv) % a.L_slab;
     u.n = unit / (a.h_kv * a.L_slab);
+    // everything is requested before anything is looked at (a workgroup that waits for one value after the other starts 1 us later)
+    const int idx = (u.n * a.L + a.layer0 + u.ls) * a.h_kv + u.h;
+    const bool fixed = FIXED && a.unit_in, list = a.stages & STAGE_LOAD_LIST, slot = a.stages & (STAGE_SCORE | STAGE_CHECK_SLOT);
     u.N = a.num_blocks[u.n];
+    const int2 in = fixed ? a.unit_in[unit] : make_int2(0, 0);
+    const int vl_in = !fixed && a.valid_len ? a.valid_len[idx] : 0, k_in = list ? a.len_in[unit] : !fixed && a.keep ? a.keep[idx] : a.budget;
+    u.slot = slot ? a.q_slot[u.n] : 0;
     u.T = u.N * a.b;
-    u.slot = 0;
-    u.k = a.budget;
-    u.vl = (u.N - 1) * a.b;
+    u.k = fixed && !list ? in.y : k_in;
+    u.vl = fixed ? in.x : a.valid_len ? vl_in : (u.N - 1) * a.b;
     u.Tv = u.vl + a.b;
     if (u.N < a.N_max || u.N > a.max_blocks) return BAD_NUM_BLOCKS;
-    const int idx = (u.n * a.L + a.layer0 + u.ls) * a.h_kv + u.h;
-    const bool fixed = FIXED && a.unit_in;
-    if (fixed || a.valid_len) {
-        u.vl = fixed ? a.unit_in[unit].x : a.valid_len[idx];
-        if (u.vl < 0 || u.vl > (u.N - 1) * a.b) return BAD_VALID_LEN;
-    }
-    u.Tv = u.vl + a.b;
+    if (u.vl < 0 || u.vl > (u.N - 1) * a.b) return BAD_VALID_LEN;
     if (u.Tv < a.w) return BAD_VALID_LEN;
-    if (a.stages & STAGE_LOAD_LIST) {
-        u.k = a.len_in[unit];
+    if (list) {
         if (u.k > a.budget) return BAD_KEEP;
     } else {
-        if (fixed) u.k = a.unit_in[unit].y;
-        else if (a.keep) u.k = a.keep[idx];
         const int cap = a.budget < u.Tv ? a.budget : u.Tv;
         if (u.k < a.w || u.k > cap) return BAD_KEEP;
     }
-    if (a.stages & (STAGE_SCORE | STAGE_CHECK_SLOT)) {
-        u.slot = a.q_slot[u.n];
-        if (u.slot < 0 || u.slot >= a.M) return BAD_SLOT;
-    }
+    if (slot && (u.slot < 0 || u.slot >= a.M)) return BAD_SLOT;
     return 0;
 }
 
-// Decode the unit, check its metadata, stage both block tables in LDS.
+// Decode the unit, check its metadata, stage the block tables in LDS (DST: that of the targets too; it is checked in any case, so that
+// all launches of a call skip the same units).
 // Returns false (for every thread alike) when the unit must be skipped.
-template <bool FIXED = false>
+template <bool FIXED = false, bool DST = true>
 __device__ inline bool unit_setup(const Args &a, int unit, Unit &u, int *tbl, int *dst, Misc *misc) {
-    const int tid = threadIdx.x, nt = blockDim.x;
+    const int tid = threadIdx.x, nt = blockDim.x, n = unit / (a.h_kv * a.L_slab);
+    const int *src = a.block_table + (size_t)n * a.max_blocks, *d = a.dst_table ? a.dst_table + (size_t)n * (a.N_max - 1) : src;
+    // the first entries are requested together with the scalars that say how many of them count
+    const int p0 = tid < a.max_blocks ? src[tid] : 0, d0 = tid < a.N_max - 1 ? d[tid] : 0;
     int bad = unit_scalars<FIXED>(a, unit, u);
     if (tid == 0) misc->bad = bad;
     __syncthreads();
     if (!bad) {
-        const int *src = a.block_table + (size_t)u.n * a.max_blocks;
         for (int i = tid; i < u.N; i += nt) {
-            int p = src[i];
+            int p = i == tid ? p0 : src[i];
             if (p < 0 || p >= a.N_total) { misc->bad = BAD_BLOCK_ID; p = 0; }
             tbl[i] = p;
         }
-        const int *d = a.dst_table ? a.dst_table + (size_t)u.n * (a.N_max - 1) : src;
         for (int i = tid; i < a.N_max - 1; i += nt) {
-            int p = d[i];
+            int p = i == tid ? d0 : d[i];
             if (p < 0 || p >= a.N_total) { misc->bad = BAD_BLOCK_ID; p = 0; }
-            dst[i] = p;
+            if (DST) dst[i] = p;
         }
     }
     __syncthreads();

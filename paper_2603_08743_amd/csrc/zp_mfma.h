@@ -40,10 +40,11 @@ namespace zp {
 // fp32), and both operands take their k index from the same bytes.  PAD: the pool's rows are shorter than ROWB; the
 // pieces beyond them are zeros in LDS and in the query fragments and add nothing.
 
-// tiles of a segment: an even number (two tiles are worked on per turn of the loops), at least four
-__device__ __forceinline__ int segment_tiles(int ntiles, int segments) {
-    const int s = 2 * ((ntiles + 2 * segments - 1) / (2 * segments));
-    return s < 4 ? 4 : s;
+// Segments of a unit with `ntiles` key tiles: as many as allowed of at least three tiles each, of equal length but for one tile; segment
+// sg starts with tile sg * ntiles / count.
+__device__ __forceinline__ int segment_count(int ntiles, int segments) {
+    const int n = (ntiles + 1) / 3;
+    return n < 1 ? 1 : (n < segments ? n : segments);
 }
 
 template <int ROWB> struct KTile {
@@ -74,7 +75,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     int uid = unit_of_block((int)blockIdx.x, (int)gridDim.x, a.xcd_map), part_no = 0;
     if (PH) { part_no = uid % a.parts; uid /= a.parts; }
     else if (a.by_cost) uid = unit_by_cost(a, (int)blockIdx.x, (int)gridDim.x, misc);
-    const bool usable = unit_setup(a, uid, u, tbl, dst, misc);
+    const bool usable = unit_setup<false, PH == 0>(a, uid, u, tbl, dst, misc);
     if (PH == 2 && part_no == 0 && threadIdx.x == 0 && a.unit_out) a.unit_out[uid] = usable ? make_int2(u.vl, u.k) : make_int2(-1, -1);
     if (!usable) return;
 
@@ -93,7 +94,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
 
     const int row_bytes = PAD ? a.row_bytes : ROWB;
 
-    for (int t = tid; t < u.T; t += NT) S[t] = 0.f;          // stale positions stay 0
+    if (!PH) for (int t = tid; t < u.T; t += NT) S[t] = 0.f;   // stale positions stay 0
     const int np = MP ? a.NP : 1;
 #pragma unroll 1
     for (int pass = 0; pass < np; pass++) {
@@ -118,18 +119,18 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
 
     const int ntiles = (u.Tv + KT - 1) / KT;
     // this workgroup's tiles [t_lo, t_hi)
-    const int seg_len = segment_tiles(ntiles, segments_of(RB));
+    const int nseg = segment_count(ntiles, segments_of(RB));
     int t_lo = 0, t_hi = ntiles;
-    if (PH) {
-        t_lo = part_no * seg_len;                             // one segment each
-        t_hi = t_lo + seg_len < ntiles ? t_lo + seg_len : ntiles;
-        if (t_lo >= ntiles) return;
+    if (PH) {                                                 // one segment each
+        if (part_no >= nseg) return;
+        t_lo = part_no * ntiles / nseg;
+        t_hi = (part_no + 1) * ntiles / nseg;
     }
     const int n_here = t_hi - t_lo;
     float2 *seg = a.seg + (size_t)u.unit * ZP_SEGMENTS * (NW * RB * 32);
-    // Key tiles travel HBM -> registers -> LDS.  Two register sets alternate so that a tile is requested two
-    // iterations before it is needed (one tile of compute is shorter than the HBM latency).
-    u32x4 stA[LPT], stB[LPT];
+    // Key tiles travel HBM -> registers -> LDS: a tile is requested when the work on the one before it starts.  A second register set,
+    // with every tile requested two iterations ahead, changed nothing at any number of units (64 to 2048 of 4112 positions).
+    u32x4 st[LPT];
     // a thread always fetches the same 16-byte piece of rows r0, r0 + RSTEP, ...: one 64-bit base, then
     // base + token * (bytes between consecutive tokens) with token = block * b + slot (fits 32 bits, host-checked)
     constexpr int RSTEP = NT / CPR;
@@ -138,7 +139,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     const char *kbase = a.k + ((size_t)u.ls * a.N_total * a.b * a.h_kv + u.h) * (size_t)row_bytes + (EVEN ? piece0 : 0);
     const unsigned tok_bytes = (unsigned)a.h_kv * row_bytes;
     const int gap = (u.N - 1) * a.b - u.vl;                   // stale positions between the live prefix and the last block
-    auto gload = [&](int tile, u32x4 (&st)[LPT], auto nt_tag) {   // rows past the end repeat the last key (masked later)
+    auto gload = [&](int tile, auto nt_tag) {   // rows past the end repeat the last key (masked later)
         // Tiles that lie wholly in the live prefix (all but the last one or two) need none of the edge handling when
         // the block size is a power of two: position = live index.  (Eight-wave workgroups only: with fewer waves a
         // thread loads eight or sixteen pieces per tile and the second copy of that code costs registers.)
@@ -176,7 +177,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         }
     };
     const int lds_st = r0 * KTl::ROW + piece0;
-    auto lstore = [&](char *buf, const u32x4 (&st)[LPT]) {
+    auto lstore = [&](char *buf) {
 #pragma unroll
         for (int i = 0; i < LPT; i++) {
             if (EVEN) *(u32x4 *)(buf + lds_st + i * RSTEP * KTl::ROW) = st[i];
@@ -186,7 +187,6 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             }
         }
     };
-    char *buf0 = kbuf, *buf1 = kbuf + KTl::BYTES;
     f32x16 zero16;
 #pragma unroll
     for (int i = 0; i < 16; i++) zero16[i] = 0.f;
@@ -286,24 +286,21 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         }
     };
     if constexpr (PH != 2) {
-    gload(t_lo, stA, ZP_NT1());
-    lstore(buf0, stA);
-    if (n_here > 1) gload(t_lo + 1, stA, ZP_NT1());
+    gload(t_lo, ZP_NT1());
+    lstore(kbuf);
     __syncthreads();
-    int sg = PH ? t_lo / seg_len : 0, seg_end = t_lo + seg_len;                            // segments have an even number of tiles, the last one aside
+    int sg = PH ? part_no : 0, seg_end = PH ? t_hi : ntiles / nseg;   // ends of segments: (sg + 1) * ntiles / nseg
+    bool fresh = true;
 #pragma unroll 1
-    for (int it = t_lo; it < t_hi; it += 2) {
-        if (it + 2 < t_hi) gload(it + 2, stB, ZP_NT1());
-        sweep1_tile(buf0, it * KT, it + seg_len == seg_end);
-        if (it + 1 < t_hi) lstore(buf1, stA);
-        __syncthreads();
-        if (it + 1 >= t_hi) break;
-        if (it + 3 < t_hi) gload(it + 3, stA, ZP_NT1());
-        sweep1_tile(buf1, (it + 1) * KT, false);
-        if (it + 2 < t_hi) lstore(buf0, stB);
-        if (it + 2 == seg_end && seg_end < t_hi) {
+    for (int it = t_lo; it < t_hi; it++) {
+        char *buf = kbuf + ((it - t_lo) & 1) * KTl::BYTES;
+        if (it + 1 < t_hi) gload(it + 1, ZP_NT1());
+        sweep1_tile(buf, it * KT, fresh);
+        if (it + 1 < t_hi) lstore(kbuf + ((it - t_lo + 1) & 1) * KTl::BYTES);
+        fresh = it + 1 == seg_end && it + 1 < t_hi;
+        if (fresh) {
             close_segment(sg++);
-            seg_end += seg_len;
+            seg_end = (sg + 1) * ntiles / nseg;
         }
         __syncthreads();
     }
@@ -318,7 +315,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             if (PH) {
                 const float2 s0 = seg[row];
                 m = s0.x, l = s0.y;
-                for (int sg = 1; sg * seg_len < ntiles; sg++) {
+                for (int sg = 1; sg < nseg; sg++) {
                     const float2 s = seg[sg * (NW * RB * 32) + row];
                     merge(m, l, s.x, s.y);
                 }
@@ -434,55 +431,47 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
 #pragma unroll
                 for (int v = 0; v < NW; v++) s += pt[v * KT + tid];
                 const int t = live_to_pos(u, a, jj);
-                if (MP) {
+                if (MP && !PH) {                            // (a split call has one pass)
                     s += S[t];
                     if (pass + 1 < np) { S[t] = s; return; }
                 }
-                S[t] = s / (float)w;
+                if (PH) a.scores_out[(size_t)u.unit * a.T_max + t] = s / (float)w;
+                else S[t] = s / (float)w;
             }
         }
     };
-    float *pt0 = part, *pt1 = part + NW * KT;
     // tiles are taken in DESCENDING order (tile number rt = t_hi-1-it): the keys sweep 1 read last are the ones
     // most likely to be still in L2 / Infinity Cache
-    gload(t_hi - 1, stA, ZP_NT2());
-    lstore(buf0, stA);
-    if (n_here > 1) gload(t_hi - 2, stA, ZP_NT2());
+    gload(t_hi - 1, ZP_NT2());
+    lstore(kbuf);
     __syncthreads();
 #pragma unroll 1
-    for (int it = 0; it < n_here; it += 2) {
-        const int rt = t_hi - 1 - it;
-        if (it + 2 < n_here) gload(rt - 2, stB, ZP_NT2());
-        sweep2_tile(buf0, pt0, rt * KT);
+    for (int it = 0; it < n_here; it++) {
+        const int rt = t_hi - 1 - it, odd = it & 1;
+        char *buf = kbuf + odd * KTl::BYTES;
+        float *pt = part + odd * (NW * KT);
+        if (it + 1 < n_here) gload(rt - 1, ZP_NT2());
+        sweep2_tile(buf, pt, rt * KT);
         if (RED) {
-            gram_first(buf0, rt * KT);
-            if (it + 1 >= n_here) gram_finish(rt * KT, nullptr, -1);
+            if (odd) gram_finish((rt + 1) * KT, buf, rt * KT);
+            else {
+                gram_first(buf, rt * KT);
+                if (it + 1 >= n_here) gram_finish(rt * KT, nullptr, -1);
+            }
         }
-        if (it + 1 < n_here) lstore(buf1, stA);
+        if (it + 1 < n_here) lstore(kbuf + (odd ^ 1) * KTl::BYTES);
         __syncthreads();
-        reduce_tile(pt0, rt * KT);
-        if (it + 1 >= n_here) break;
-        if (it + 3 < n_here) gload(rt - 3, stA, ZP_NT2());
-        sweep2_tile(buf1, pt1, (rt - 1) * KT);
-        if (RED) gram_finish(rt * KT, buf1, (rt - 1) * KT);
-        if (it + 2 < n_here) lstore(buf0, stB);
-        __syncthreads();
-        reduce_tile(pt1, (rt - 1) * KT);
+        reduce_tile(pt, rt * KT);
     }
-    __syncthreads();
-    if (PH) {                                                // (one pass) this part's scores; the first part clears what is not live
-        float *o = a.scores_out + (size_t)u.unit * a.T_max;
-        const int j1 = t_hi * KT < u.Tv ? t_hi * KT : u.Tv;
-        for (int j = t_lo * KT + tid; j < j1; j += NT) {
-            const int t = live_to_pos(u, a, j);
-            o[t] = S[t];
-        }
+    if (PH) {                                                // (one pass) the first part clears what is not live
         if (part_no == 0) {
+            float *o = a.scores_out + (size_t)u.unit * a.T_max;
             for (int t = u.vl + tid; t < (u.N - 1) * a.b; t += NT) o[t] = 0.f;
             for (int t = u.T + tid; t < a.T_max; t += NT) o[t] = 0.f;
         }
         return;
     }
+    __syncthreads();
     }
     unit_tail<ROWB, DT, PAD, REF, NW, ZP_WPE(NW, RB, ROWB) == 4>(a, u, smem, tbl, dst, misc);
 }
