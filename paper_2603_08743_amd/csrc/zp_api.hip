@@ -275,22 +275,43 @@ static bool overlaps_scalars(const zp::Args &a, long long units) {
     return len_out_meets(a, units, a.valid_len, n) || len_out_meets(a, units, a.keep, n);
 }
 
-// Workgroups per unit of the two scoring launches (0: one launch does everything).
-static int split_parts(const zp_ctx *ctx, const zp::Args &a, Path path, const zp::MfmaGeo &geo, hipStream_t s) {
+// Whether a call is split.
+static bool is_split(const zp_ctx *ctx, const zp::Args &a, Path path, const zp::MfmaGeo &geo, hipStream_t s) {
     const long long units = (long long)a.B * a.L_slab * a.h_kv;
     if (path != PATH_MFMA || geo.NP != 1 || a.ex || !ctx->slot[0].mem || units <= 0 || !few_units(ctx, units) ||
         !split_pays(ctx->n_cu, units, a.T_max, geo, a.dtype == 0, (a.stages & zp::STAGE_SELECT) != 0, a.valid_len != nullptr))
-        return 0;
-    if (workspace_bytes(a, geo, units) > kSlotBytes || overlaps_tables(a, units)) return 0;
+        return false;
+    if (workspace_bytes(a, geo, units) > kSlotBytes || overlaps_tables(a, units)) return false;
     int dev = -1;                                              // workspaces and events belong to the context's GPU
     if ((s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) != hipSuccess) (void)hipGetLastError();
-    if (dev != ctx->device) return 0;
+    if (dev != ctx->device) return false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
         (void)hipGetLastError();                               // not the launch's error
-        return 0;
+        return false;
     }
-    return cap == hipStreamCaptureStatusNone ? zp::segments_of(geo.RB) : 0;   // a graph may run beside anything: no shared workspace
+    return cap == hipStreamCaptureStatusNone;                  // a graph may run beside anything: no shared workspace
+}
+
+// Workgroups per unit of the two scoring launches.  A compute unit takes K = units x parts / compute units of them (the fullest one), in
+// as many rounds as its registers and LDS ask for.  A round costs its set-up and first loads, about as much as 21 tiles of one query
+// block; a tile costs a compute unit the query blocks of the workgroups on it, but with fewer than six blocks at work there its latency.
+// The cheapest number against as many parts as segments, in us: fp32 128 units of 1040 (four waves) 163 against 190, staged 192 units of 2064
+// to 4112 (w 32) 193 against 201, one wave 192 units of 4112 284 against 301, 128 units (w 64) 210 against 223, 64 units 119 against 122;
+// 128 units of two waves (w 16) keep eight: 174 against 190 with four.
+static int pick_parts(const zp_ctx *ctx, const zp::Args &a, const zp::MfmaGeo &geo, long long units, int lds_bytes) {
+    const int kt = zp::mfma_tile_keys(geo.rowb), ntiles = (a.T_max + kt - 1) / kt, nseg = zp::segment_count(ntiles, zp::segments_of(geo.RB));
+    const int per_simd = geo.RB > 1 || geo.rowb > 512 ? 2 : geo.rowb > 256 ? 3 : 4;
+    const int by_regs = 4 * per_simd / geo.NW > 0 ? 4 * per_simd / geo.NW : 1, by_lds = kLdsLimit / lds_bytes, at_once = by_regs < by_lds ? by_regs : by_lds;
+    int best = 1;
+    long long cost = -1;
+    for (int parts = 1; parts <= nseg; parts++) {
+        const long long K = (units * parts + ctx->n_cu - 1) / ctx->n_cu, rounds = (K + at_once - 1) / at_once, work = K * geo.NW * geo.RB;
+        const long long tiles = (long long)((nseg + parts - 1) / parts) * ((ntiles + nseg - 1) / nseg);
+        const long long c = tiles * (work > 6 * rounds ? work : 6 * rounds) + 21 * rounds;
+        if (cost < 0 || c < cost) { cost = c; best = parts; }
+    }
+    return best;
 }
 
 // Row-moving workgroups per unit: K and V apart, rows cut into the shortest pieces (from 128 bytes on, 64 where those do not divide
@@ -312,7 +333,7 @@ static void pick_slices(const zp_ctx *ctx, zp::Args *a, int units) {
         }
 }
 
-static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, const zp::MfmaGeo &geo, hipStream_t s) {
+static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int units, const zp::MfmaGeo &geo, hipStream_t s) {
     std::lock_guard<std::mutex> lock(ctx->slot_mu);
     int i = -1;
     for (int j = 0; j < ZP_SLOTS; j++) if (ctx->slot[j].used && ctx->slot[j].stream == (void *)s) i = j;
@@ -329,11 +350,11 @@ static hipError_t launch_split(zp_ctx *ctx, zp::Args a, int parts, int units, co
     m.seg = (float2 *)w.mem;
     m.unit_out = whole && overlaps_scalars(a, units) ? scalars : nullptr;
     m.scores_out = scores;
-    m.parts = parts;
     m.off_tbl = 0;                                            // the two scoring launches keep no scores and no targets on chip
     m.off_misc = align16(a.max_blocks * 4);
     m.off_union = m.off_misc + kMiscBytes;
     m.lds_bytes = align16(m.off_union + (int)zp::mfma_union_bytes(geo));
+    m.parts = pick_parts(ctx, a, geo, units, m.lds_bytes);
     w.used = true;
     w.stream = (void *)s;
     for (m.phase = 1; m.phase <= 2 && e == hipSuccess; m.phase++) e = zp::launch_unit_mfma(m, units, geo, s);
@@ -370,9 +391,9 @@ extern "C" int32_t zp_last_launches(const zp_ctx *ctx) { return ctx ? ctx->launc
 static zp_status launch(zp_ctx *ctx, const char *who, zp::Args &a, Path path, const zp::MfmaGeo &geo, void *stream) {
     const int units = a.B * a.L_slab * a.h_kv;
     ctx->launches = units > 0;
-    if (const int parts = split_parts(ctx, a, path, geo, (hipStream_t)stream)) {
+    if (is_split(ctx, a, path, geo, (hipStream_t)stream)) {
         ctx->launches = (a.stages & zp::STAGE_SELECT) ? 3 : 2;
-        const hipError_t e = launch_split(ctx, a, parts, units, geo, (hipStream_t)stream);
+        const hipError_t e = launch_split(ctx, a, units, geo, (hipStream_t)stream);
         if (e != hipSuccess) return fail(ctx, ZP_EHIP, "%s: kernel launch failed: %s", who, hipGetErrorString(e));
         return ZP_OK;
     }

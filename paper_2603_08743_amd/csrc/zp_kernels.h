@@ -64,9 +64,9 @@ struct Args {
     // byte offsets into dynamic LDS
     int off_S, off_tbl, off_dst, off_misc, off_union, lds_bytes;
     int NP;                                    // matrix-core kernel: passes over the keys (padded rows only)
-    // few units: several workgroups per unit, one launch per dependency (the rule and its figures: split_parts in zp_api.hip)
+    // few units: several workgroups per unit, one launch per dependency (the rules and their figures: split_pays and pick_parts in zp_api.hip)
     int phase;                                 // matrix-core kernel: 0 whole unit, 1 sweep 1 of a part, 2 sweep 2 of a part
-    int parts;                                 // workgroups per unit (phases 1 and 2)
+    int parts;                                 // workgroups per unit (phases 1 and 2), each taking whole segments
     float2 *seg;                               // [units][ZP_SEGMENTS][query rows, padded]: (reference, sum) of sweep 1 per segment
     int2 *unit_out; const int2 *unit_in;       // [units]: (live prefix length, keep count) of every unit, written by phase 2, read by the launch after it
     int slices, slice_bytes;                   // row-moving kernel: workgroups per unit, bytes of a row each of them moves
@@ -95,6 +95,12 @@ hipError_t launch_unit_sliced(const Args &a, int units, hipStream_t s);
 // the second look: eight runs cost 0.9 %).
 #define ZP_SEGMENTS 8
 constexpr __host__ __device__ int segments_of(int RB) { return RB > 1 ? 4 : ZP_SEGMENTS; }
+// Runs of a unit with `ntiles` key tiles: as many as allowed of at least three tiles each, of equal length but for one tile; run
+// sg starts with tile sg * ntiles / count.
+constexpr __host__ __device__ int segment_count(int ntiles, int segments) {
+    const int n = (ntiles + 1) / 3;
+    return n < 1 ? 1 : (n < segments ? n : segments);
+}
 // Geometry of the matrix-core kernel for a launch: waves per workgroup, 32-row query blocks per wave, passes over the keys,
 // row bytes of the instantiation and whether the pool's rows are shorter than that.
 struct MfmaGeo { int NW, RB, NP, rowb; bool pad; };

@@ -40,13 +40,6 @@ namespace zp {
 // fp32), and both operands take their k index from the same bytes.  PAD: the pool's rows are shorter than ROWB; the
 // pieces beyond them are zeros in LDS and in the query fragments and add nothing.
 
-// Segments of a unit with `ntiles` key tiles: as many as allowed of at least three tiles each, of equal length but for one tile; segment
-// sg starts with tile sg * ntiles / count.
-__device__ __forceinline__ int segment_count(int ntiles, int segments) {
-    const int n = (ntiles + 1) / 3;
-    return n < 1 ? 1 : (n < segments ? n : segments);
-}
-
 template <int ROWB> struct KTile {
     static constexpr int KT = mfma_tile_keys(ROWB);
     static constexpr int ROW = ROWB + 16;         // padded row stride in bytes: conflict-free 16-byte fragment reads
@@ -121,16 +114,26 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     // this workgroup's tiles [t_lo, t_hi)
     const int nseg = segment_count(ntiles, segments_of(RB));
     int t_lo = 0, t_hi = ntiles;
-    if (PH) {                                                 // one segment each
-        if (part_no >= nseg) return;
-        t_lo = part_no * ntiles / nseg;
-        t_hi = (part_no + 1) * ntiles / nseg;
+    int sg_lo = 0;
+    if (PH) {                                                 // whole segments
+        sg_lo = part_no * nseg / a.parts;
+        const int sg_hi = (part_no + 1) * nseg / a.parts;
+        if (sg_lo == sg_hi) return;
+        t_lo = sg_lo * ntiles / nseg;
+        t_hi = sg_hi * ntiles / nseg;
     }
     const int n_here = t_hi - t_lo;
     float2 *seg = a.seg + (size_t)u.unit * ZP_SEGMENTS * (NW * RB * 32);
-    // Key tiles travel HBM -> registers -> LDS: a tile is requested when the work on the one before it starts.  A second register set,
-    // with every tile requested two iterations ahead, changed nothing at any number of units (64 to 2048 of 4112 positions).
-    u32x4 st[LPT];
+    // Key tiles travel HBM -> registers -> LDS.  With one query block per wave a tile is requested when the work on the one before it
+    // starts: a second register set, with every tile requested two turns ahead, changed nothing from 64 to 2048 units of 4112
+    // positions and cost up to 130 registers.  With two or three blocks per wave one workgroup has the compute unit to itself and
+    // the second set (DEEP) gives 3 % (160 units of 3440, G 4, w 72: 270 -> 262 us).  Loops of two tiles a turn (TWO) where a wave holds
+    // several blocks (44 units of 9136, G 7, w 108: 508 -> 401 us) and with redundancy in the launch (448 units of 5200: 949 -> 921 us);
+    // everywhere else one tile a turn is as fast, and one wave with two is four times slower.
+    constexpr bool TWO = RB > 1 || REF >= 2, DEEP = RB == 2 || (RB == 3 && REF != 3);
+    u32x4 stA[LPT], stB[LPT];                                 // named by type: passed by reference, the padded kernels take up to 180 registers more
+    using SetA = std::false_type;
+    using SetB = std::true_type;
     // a thread always fetches the same 16-byte piece of rows r0, r0 + RSTEP, ...: one 64-bit base, then
     // base + token * (bytes between consecutive tokens) with token = block * b + slot (fits 32 bits, host-checked)
     constexpr int RSTEP = NT / CPR;
@@ -139,7 +142,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     const char *kbase = a.k + ((size_t)u.ls * a.N_total * a.b * a.h_kv + u.h) * (size_t)row_bytes + (EVEN ? piece0 : 0);
     const unsigned tok_bytes = (unsigned)a.h_kv * row_bytes;
     const int gap = (u.N - 1) * a.b - u.vl;                   // stale positions between the live prefix and the last block
-    auto gload = [&](int tile, auto nt_tag) {   // rows past the end repeat the last key (masked later)
+    auto gload = [&](int tile, auto set, auto nt_tag) __attribute__((always_inline)) {   // rows past the end repeat the last key (masked later)
+        u32x4 (&st)[LPT] = decltype(set)::value ? stB : stA;
         // Tiles that lie wholly in the live prefix (all but the last one or two) need none of the edge handling when
         // the block size is a power of two: position = live index.  (Eight-wave workgroups only: with fewer waves a
         // thread loads eight or sixteen pieces per tile and the second copy of that code costs registers.)
@@ -177,7 +181,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         }
     };
     const int lds_st = r0 * KTl::ROW + piece0;
-    auto lstore = [&](char *buf) {
+    auto lstore = [&](char *buf, auto set) __attribute__((always_inline)) {
+        const u32x4 (&st)[LPT] = decltype(set)::value ? stB : stA;
 #pragma unroll
         for (int i = 0; i < LPT; i++) {
             if (EVEN) *(u32x4 *)(buf + lds_st + i * RSTEP * KTl::ROW) = st[i];
@@ -198,7 +203,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     // The sum of exp2(x - ref) is kept against a per-row reference `rm` that only moves when the sum leaves the
     // safe range (first subtile, or logits that jump by more than ~2^100): then the subtile is redone with the
     // proper maximum.  This keeps the common path free of the max reduction: fma, exp2, add per logit.
-    auto sweep1_body = [&](const char *buf, int j0, bool fresh, auto edge_tag) {   // fresh: a segment's first tile
+    auto sweep1_body = [&](const char *buf, int j0, bool fresh, auto edge_tag) __attribute__((always_inline)) {   // fresh: a segment's first tile
         constexpr bool edge = decltype(edge_tag)::value;
 #pragma unroll
         for (int sub = 0; sub < KT / 32; sub++) {
@@ -248,7 +253,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             }
         }
     };
-    auto sweep1_tile = [&](const char *buf, int j0, bool fresh) {
+    auto sweep1_tile = [&](const char *buf, int j0, bool fresh) __attribute__((always_inline)) {
         if (j0 + KT > u.Tv - w) sweep1_body(buf, j0, fresh, std::true_type());
         else sweep1_body(buf, j0, fresh, std::false_type());
     };
@@ -259,7 +264,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         l = fmaf(l, fexp2(m - mm), l2 * fexp2(m2 - mm));
         m = mm;
     };
-    auto close_segment = [&](int sg) {
+    auto close_segment = [&](int sg) __attribute__((always_inline)) {
         // With eight waves the addresses below stay out of the tile loop (12 spilled registers with REF 2, 26 without).  Fewer waves have
         // the registers, and there the barrier makes the loop wait for its loads: 512 units of 4112 positions with the fused redundancy
         // (one wave, G 4, w 8) 1193 against 1052 us, with the separate one (d 64, two waves, blocks of 32) 176 against 170 us at 528.
@@ -286,23 +291,33 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         }
     };
     if constexpr (PH != 2) {
-    gload(t_lo, ZP_NT1());
-    lstore(kbuf);
+    gload(t_lo, SetA(), ZP_NT1());
+    lstore(kbuf, SetA());
+    if (DEEP && t_lo + 1 < t_hi) gload(t_lo + 1, SetA(), ZP_NT1());
     __syncthreads();
-    int sg = PH ? part_no : 0, seg_end = PH ? t_hi : ntiles / nseg;   // ends of segments: (sg + 1) * ntiles / nseg
+    int sg = sg_lo, seg_end = (sg + 1) * ntiles / nseg;
     bool fresh = true;
-#pragma unroll 1
-    for (int it = t_lo; it < t_hi; it++) {
-        char *buf = kbuf + ((it - t_lo) & 1) * KTl::BYTES;
-        if (it + 1 < t_hi) gload(it + 1, ZP_NT1());
-        sweep1_tile(buf, it * KT, fresh);
-        if (it + 1 < t_hi) lstore(kbuf + ((it - t_lo + 1) & 1) * KTl::BYTES);
+    // a tile of the buffer `odd`; `next` holds the one after it (DEEP: by now, and `far` takes the one after that)
+    auto turn1 = [&](int it, int odd, auto next, auto far) __attribute__((always_inline)) {
+        if (it + (DEEP ? 2 : 1) < t_hi) gload(it + (DEEP ? 2 : 1), std::conditional_t<DEEP, decltype(far), decltype(next)>(), ZP_NT1());
+        sweep1_tile(kbuf + odd * KTl::BYTES, it * KT, fresh);
+        if (it + 1 < t_hi) lstore(kbuf + (odd ^ 1) * KTl::BYTES, next);
         fresh = it + 1 == seg_end && it + 1 < t_hi;
         if (fresh) {
             close_segment(sg++);
             seg_end = (sg + 1) * ntiles / nseg;
         }
         __syncthreads();
+    };
+    if constexpr (TWO) {
+#pragma unroll 1
+        for (int it = t_lo; it < t_hi; it += 2) {
+            turn1(it, 0, SetA(), SetB());
+            if (it + 1 < t_hi) turn1(it + 1, 1, std::conditional_t<DEEP, SetB, SetA>(), SetA());
+        }
+    } else {
+#pragma unroll 1
+        for (int it = t_lo; it < t_hi; it++) turn1(it, (it - t_lo) & 1, SetA(), SetB());
     }
     close_segment(sg);
     if (PH == 1) return;
@@ -343,7 +358,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     }
     // max_g exp2(x_g - lse_g) = exp2(c max_g (x_g - lse_g) / c): the maximum over the group is taken before the
     // exponential (c > 0), so a window row costs one multiply and one exp2 instead of G of each.
-    auto sweep2_body = [&](const char *buf, float *pt, int j0, auto edge_tag) {
+    auto sweep2_body = [&](const char *buf, float *pt, int j0, auto edge_tag) __attribute__((always_inline)) {
         constexpr bool edge = decltype(edge_tag)::value;
 #pragma unroll
         for (int sub = 0; sub < KT / 32; sub++) {
@@ -397,7 +412,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     const float inv_len = 1.0f / (float)u.Tv;
     constexpr int PER = KT / 16, HOLD = (PER + NW - 1) / NW;  // blocks per tile; first-tile blocks one wave takes
     f32x4 gacc[HOLD];
-    auto gram_first = [&](const char *buf, int j0) {
+    auto gram_first = [&](const char *buf, int j0) __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < HOLD; h++) {
             const int q = wv + h * NW;
@@ -405,7 +420,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         }
     };
     // jA: live index of the first tile (products held in gacc); bufB / jB: the second tile, jB < 0 if there is none
-    auto gram_finish = [&](int jA, const char *bufB, int jB) {
+    auto gram_finish = [&](int jA, const char *bufB, int jB) __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < HOLD; h++) {
             const int q = wv + h * NW;
@@ -419,11 +434,11 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             }
         }
     };
-    auto sweep2_tile = [&](const char *buf, float *pt, int j0) {
+    auto sweep2_tile = [&](const char *buf, float *pt, int j0) __attribute__((always_inline)) {
         if (j0 + KT > u.Tv - w) sweep2_body(buf, pt, j0, std::true_type());
         else sweep2_body(buf, pt, j0, std::false_type());
     };
-    auto reduce_tile = [&](const float *pt, int j0) {         // fixed-order sum over the waves: deterministic
+    auto reduce_tile = [&](const float *pt, int j0) __attribute__((always_inline)) {         // fixed-order sum over the waves: deterministic
         if (tid < KT) {
             const int jj = j0 + tid;
             if (jj < u.Tv) {
@@ -442,15 +457,15 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     };
     // tiles are taken in DESCENDING order (tile number rt = t_hi-1-it): the keys sweep 1 read last are the ones
     // most likely to be still in L2 / Infinity Cache
-    gload(t_hi - 1, ZP_NT2());
-    lstore(kbuf);
+    gload(t_hi - 1, SetA(), ZP_NT2());
+    lstore(kbuf, SetA());
+    if (DEEP && n_here > 1) gload(t_hi - 2, SetA(), ZP_NT2());
     __syncthreads();
-#pragma unroll 1
-    for (int it = 0; it < n_here; it++) {
-        const int rt = t_hi - 1 - it, odd = it & 1;
-        char *buf = kbuf + odd * KTl::BYTES;
+    auto turn2 = [&](int it, int odd, auto next, auto far) __attribute__((always_inline)) {
+        const int rt = t_hi - 1 - it;
+        const char *buf = kbuf + odd * KTl::BYTES;
         float *pt = part + odd * (NW * KT);
-        if (it + 1 < n_here) gload(rt - 1, ZP_NT2());
+        if (it + (DEEP ? 2 : 1) < n_here) gload(rt - (DEEP ? 2 : 1), std::conditional_t<DEEP, decltype(far), decltype(next)>(), ZP_NT2());
         sweep2_tile(buf, pt, rt * KT);
         if (RED) {
             if (odd) gram_finish((rt + 1) * KT, buf, rt * KT);
@@ -459,12 +474,22 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
                 if (it + 1 >= n_here) gram_finish(rt * KT, nullptr, -1);
             }
         }
-        if (it + 1 < n_here) lstore(kbuf + (odd ^ 1) * KTl::BYTES);
+        if (it + 1 < n_here) lstore(kbuf + (odd ^ 1) * KTl::BYTES, next);
         __syncthreads();
         reduce_tile(pt, rt * KT);
+    };
+    if constexpr (TWO) {
+#pragma unroll 1
+        for (int it = 0; it < n_here; it += 2) {
+            turn2(it, 0, SetA(), SetB());
+            if (it + 1 < n_here) turn2(it + 1, 1, std::conditional_t<DEEP, SetB, SetA>(), SetA());
+        }
+    } else {
+#pragma unroll 1
+        for (int it = 0; it < n_here; it++) turn2(it, it & 1, SetA(), SetB());
     }
-    if (PH) {                                                // (one pass) the first part clears what is not live
-        if (part_no == 0) {
+    if (PH) {                                                // (one pass) the last part, which is never empty, clears what is not live
+        if (part_no == a.parts - 1) {
             float *o = a.scores_out + (size_t)u.unit * a.T_max;
             for (int t = u.vl + tid; t < (u.N - 1) * a.b; t += NT) o[t] = 0.f;
             for (int t = u.T + tid; t < a.T_max; t += NT) o[t] = 0.f;
