@@ -112,6 +112,15 @@ extern "C" zp_status zp_set_option(zp_ctx *ctx, int32_t option, int32_t value) {
     return ZP_EINVAL;
 }
 
+// Lightning redundancy in blocks of more than 32: a workgroup has at least four waves, above 96 positions eight, also where the window
+// gives fewer waves query blocks (the others leave the scoring arithmetic out), and goes block by block with the rows in LDS
+// (redundancy_staged) where a block has column groups of 32 for at least half the waves.  Fragments straight from L2 against this,
+// in us: paper geometry (two query blocks, blocks of 256, 1152 units of 2304) 1692:951, with two waves 1384; 512 units of 2176 in
+// blocks of 128 (one query block) 880:383; 512 units of 4160 in blocks of 64, four waves 1183:884; with eight waves blocks of 64 keep
+// two waves busy and stay with redundancy_blocks (1006:1028, the larger kernel).
+static int red_waves(int b) { return b > 96 ? 8 : b > 32 ? 4 : 1; }
+static bool red_staged(int b, int NW) { return b > 32 && 2 * ((b + 31) / 32) >= NW; }
+
 // Scalar checks shared by every call, and the kernel argument block.  `need_q`: the call scores.
 static zp_status prepare(zp_ctx *ctx, const char *who, const zp_pool *p, const zp_batch *b, bool need_q, zp::Args *a,
                          Path *path, zp::MfmaGeo *geo, const zp_extras *ex = nullptr, bool fused = false) {
@@ -159,6 +168,7 @@ static zp_status prepare(zp_ctx *ctx, const char *who, const zp_pool *p, const z
     }
     // score refinements (they run in the tail of the one-workgroup-per-unit kernels only)
     if (ex) {
+        if (*path == PATH_MFMA && ex->lambda != 0.f && geo->RB == 1 && geo->NW < red_waves(p->b)) geo->NW = red_waves(p->b);
         if (ex->pool_kernel < 1 || !(ex->pool_kernel & 1)) return fail(ctx, ZP_EINVAL, "%s: pool_kernel %d must be odd and >= 1", who, ex->pool_kernel);
         if (ex->lambda != 0.f && !(ex->tau > 0.f && std::isfinite(ex->tau))) return fail(ctx, ZP_EINVAL, "%s: tau must be positive", who);
         if (ex->F && (long long)p->L_slab * p->N_total * p->b * p->h_kv > 0xffffffffLL)
@@ -178,7 +188,10 @@ static zp_status prepare(zp_ctx *ctx, const char *who, const zp_pool *p, const z
         // similarity tiles from sweep 2's key tiles
         if ((a->ex & zp::EX_RED) && mf && !geo->pad && p->b == 16 && geo->RB == 1) a->ex |= zp::EX_RED_FUSED;
         const size_t score_bytes = !need_q ? 0 : mf ? zp::mfma_union_bytes(*geo) : (size_t)a->G * a->w * 4;
-        const size_t red_bytes = mf && 32 % p->b == 0 ? (size_t)geo->NW * 96 * 4 : (size_t)a->T_max * 12;
+        if ((a->ex & zp::EX_RED) && mf && red_staged(p->b, geo->NW)) a->ex |= zp::EX_RED_STAGED;
+        else a->ex &= ~zp::EX_RED_STAGED;
+        const size_t red_bytes = a->ex & zp::EX_RED_STAGED ? 12 + 12 * (size_t)((p->b + 31) & ~31) + (size_t)zp::mfma_tile_keys(geo->rowb) * (geo->rowb + 16)
+                                 : mf && 32 % p->b == 0 ? (size_t)geo->NW * 96 * 4 : (size_t)a->T_max * 12;
         const size_t refine_bytes = ((a->ex & (zp::EX_POOL | zp::EX_RED)) ? (size_t)a->T_max * 4 : 0) + ((a->ex & zp::EX_RED) ? red_bytes : 0);
         const size_t list_bytes = (size_t)a->budget * 4;
         a->off_S = 0;

@@ -697,7 +697,7 @@ __device__ inline void redundancy_mfma(const Args &a, const Unit &u, const int *
     __syncthreads();
 }
 
-// Any other block size on the matrix cores.  The similarity matrix of one block is cut into 32-column groups; a wave owns a
+// Other block sizes on the matrix cores (those that redundancy_staged does not take).  The similarity matrix of one block is cut into 32-column groups; a wave owns a
 // group and goes through the block's 32-row groups, own rows first, each one 32x32 tile (lane L holds column L%32, 16 of the
 // rows).  A column's sum and the last row above p stay in its two lanes over all tiles; the matrix is symmetric, so the sum of
 // column r is the sum of row r before zeroing, and what was zeroed in row r is taken off in a pass of its own (waves go
@@ -878,6 +878,156 @@ __device__ inline void redundancy_blocks(const Args &a, const Unit &u, const int
     __syncthreads();
 }
 
+// Large blocks, block by block: every wave holds the fragments of up to CW 32-column groups of the block in registers, the block's rows
+// go through LDS (SR at a time, the next ones requested before the current ones are worked on) and all waves read their row fragments
+// from there.  Fragments straight from memory touch 32 rows for 32 bytes each, and every row group was fetched once per column
+// group: 512 units of 4352 positions in blocks of 256 (d 128, w 64) 1518 -> 859 us, of 4224 in blocks of 128 1148 -> 845.  Four column groups
+// per wave need more than 256 registers, two with 256-byte rows fit them.
+// A similarity is (product * 1 / row norm) * 1 / column norm; the column's factor is taken out of the sum.  Rows that count as zero (norm 0 or
+// infinite, not live) are staged as zeros, columns that do are left out at the end.  inv, zr, zv: LDS, by row of the block.
+template <int ROWB, int DT, bool PAD, int NW, int CW>
+__device__ inline void redundancy_staged(const Args &a, const Unit &u, const int *tbl, float *rs, float *inv, int *zr, float *zv, char *stage) {
+    constexpr int KK = ROWB / 32, CPR = ROWB / 16, SR = mfma_tile_keys(ROWB), ROW = ROWB + 16, NT = NW * 64, LPT = (SR * CPR + NT - 1) / NT;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
+    const int b = a.b, ncg = (b + 31) >> 5;
+    const float inv_len = 1.0f / (float)u.Tv;
+    const size_t slot_bytes = (size_t)a.h_kv * a.row_bytes;
+    const int dgi = ((l32 >> 3) << 2) | (l32 & 3);              // register that holds the diagonal entry ...
+    const bool dg_mine = hf == ((l32 >> 2) & 1);                // ... in this half of the wave
+    f32x16 zero16;
+#pragma unroll
+    for (int i = 0; i < 16; i++) zero16[i] = 0.f;
+    u32x4 col[CW][KK], st[LPT];
+#pragma unroll 1
+    for (int blk = 0; blk < u.N; blk++) {
+        const int live = blk == u.N - 1 ? b : u.vl - blk * b < b ? u.vl - blk * b : b, j0 = blk == u.N - 1 ? u.vl : blk * b;
+        if (live <= 0) continue;
+        const char *base = a.k + row_off(a, u.ls, tbl[blk], 0, u.h);
+        auto load_cols = [&](int g0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < CW; c++) {
+                const int r = (g0 + wv + c * NW) * 32 + l32;
+                load_row<ROWB, PAD>(base + (r < b ? r : b - 1) * slot_bytes, hf, a.row_bytes, col[c]);
+            }
+        };
+        // inverse norms from the diagonals
+#pragma unroll 1
+        for (int g0 = 0; g0 < ncg; g0 += NW * CW) {
+            load_cols(g0);
+#pragma unroll
+            for (int c = 0; c < CW; c++) {
+                const int r = (g0 + wv + c * NW) * 32 + l32;
+                f32x16 acc = zero16;
+#pragma unroll
+                for (int kk = 0; kk < KK; kk++) acc = mma32<DT>(col[c][kk], col[c][kk], acc);
+                float dg = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; i++) dg = i == dgi ? acc[i] : dg;
+                if (dg_mine && r < ncg * 32) inv[r] = (r < live && dg > 0.f) ? 1.0f / sqrtf(dg) : 0.f;
+            }
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int g0 = 0; g0 < ncg; g0 += NW * CW) {
+            if (ncg > NW * CW) load_cols(g0);
+            float ic[CW], csum[CW], lastv[CW];
+            int last[CW];
+#pragma unroll
+            for (int c = 0; c < CW; c++) {
+                const int g = g0 + wv + c * NW;
+                ic[c] = g < ncg ? inv[g * 32 + l32] : 0.f;
+                csum[c] = lastv[c] = 0.f;
+                last[c] = -1;
+            }
+            auto gload = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < LPT; i++) {
+                    const int pc = tid + i * NT, row = pc / CPR, off = (pc - row * CPR) * 16, r = r0 + row < b ? r0 + row : b - 1;
+                    st[i] = u32x4{0u, 0u, 0u, 0u};
+                    if ((SR * CPR % NT == 0 || row < SR) && (!PAD || off < a.row_bytes)) st[i] = *(const u32x4 *)(base + r * slot_bytes + off);
+                }
+            };
+            gload(0);
+#pragma unroll 1
+            for (int r0 = 0; r0 < b; r0 += SR) {
+                __syncthreads();                                 // the rows before these have been read
+#pragma unroll
+                for (int i = 0; i < LPT; i++) {
+                    const int pc = tid + i * NT, row = pc / CPR;
+                    const float n = r0 + row < ncg * 32 ? inv[r0 + row] : 0.f;
+                    if (SR * CPR % NT == 0 || row < SR) *(u32x4 *)(stage + row * ROW + (pc - row * CPR) * 16) = n != 0.f ? st[i] : u32x4{0u, 0u, 0u, 0u};
+                }
+                __syncthreads();
+                if (r0 + SR < b) gload(r0 + SR);
+#pragma unroll 1
+                for (int rg = r0; rg < r0 + SR && rg < b; rg += 32) {
+                    f32x4 ir[4];
+#pragma unroll
+                    for (int q = 0; q < 4; q++) ir[q] = *(const f32x4 *)(inv + rg + 4 * hf + 8 * q);
+                    const char *rp = stage + (rg - r0 + l32) * ROW + hf * 16;
+#pragma unroll
+                    for (int c = 0; c < CW; c++) {
+                        const int g = g0 + wv + c * NW;
+                        if (g >= ncg) break;
+                        f32x16 acc = zero16;
+#pragma unroll
+                        for (int kk = 0; kk < KK; kk++) acc = mma32<DT>(*(const u32x4 *)(rp + kk * 32), col[c][kk], acc);
+                        if (g * 32 == rg) {
+#pragma unroll
+                            for (int i = 0; i < 16; i++) acc[i] = dg_mine && i == dgi ? 0.f : acc[i];
+                        }
+                        float mx = -INFINITY;
+#pragma unroll
+                        for (int i = 0; i < 16; i++) {
+                            acc[i] *= ir[i >> 2][i & 3];
+                            csum[c] += acc[i];
+                            mx = fmaxf(mx, acc[i]);
+                        }
+                        if (__any((ic[c] != 0.f ? mx * ic[c] : 0.f) > a.p_thr)) {
+#pragma unroll
+                            for (int i = 0; i < 16; i++) {       // rows ascend with i
+                                const int r = rg + 4 * hf + 8 * (i >> 2) + (i & 3);
+                                const float v = ic[c] != 0.f ? acc[i] * ic[c] : 0.f;
+                                if (v > a.p_thr && r < b) { last[c] = r; lastv[c] = v; }
+                            }
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < CW; c++) {
+                const int r = (g0 + wv + c * NW) * 32 + l32;
+                const int o_last = __shfl_xor(last[c], 32);
+                const float o_lastv = __shfl_xor(lastv[c], 32), sum = csum[c] + __shfl_xor(csum[c], 32);
+                if (hf == 0 && r < b) {
+                    zr[r] = r < live ? (o_last > last[c] ? o_last : last[c]) : -1;
+                    zv[r] = o_last > last[c] ? o_lastv : lastv[c];
+                    if (r < live) rs[j0 + r] = ic[c] != 0.f ? sum * ic[c] : 0.f;
+                }
+            }
+        }
+        __syncthreads();
+        // symmetric matrix: the sum of column r is the sum of row r before zeroing; take off what was zeroed in row r
+        for (int r0 = wv * 64; r0 < live; r0 += NT) {
+            const int r = r0 + lane;
+            float corr = 0.f;
+            for (int c0 = 0; c0 < b; c0 += 64) {
+                const int row = c0 + lane < b ? zr[c0 + lane] : -1;
+                const float val = c0 + lane < b ? zv[c0 + lane] : 0.f;
+                unsigned long long m = __ballot(row >= 0);
+                while (m) {                                      // columns ascend
+                    const int l = __builtin_ctzll(m);
+                    m &= m - 1;
+                    const float v = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, val), l));
+                    corr += __builtin_amdgcn_readlane(row, l) == r ? v : 0.f;
+                }
+            }
+            if (r < live) rs[j0 + r] = (rs[j0 + r] - corr) * inv_len;
+        }
+        __syncthreads();
+    }
+}
+
 // Block size 16, live prefix: the similarity matrix of one block from the key tile that sweep 2 holds in LDS anyway
 // (rows `rows`, ROWB bytes apart, 16 keys of one block).  K_blk K_blk^T is one 16x16 tile of the matrix cores
 // (v_mfma_f32_16x16x32_bf16, both operands the same fragments: lane L supplies key L%16, elements 8*(L/16).. of every
@@ -993,6 +1143,11 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
             redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, true);
         } else if (ROWB > 0 && 32 % a.b == 0) {
             if constexpr (ROWB > 0) redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, false);
+        } else if (ROWB > 0 && NW >= 4 && (a.ex & EX_RED_STAGED)) {
+            const int rows = (a.b + 31) & ~31;
+            float *inv = tmp + ((a.T_max + 3) & ~3);
+            constexpr int CW = ROWB > 256 || TIGHT ? 1 : ROWB > 128 ? 2 : NW > 4 ? 1 : 4;
+            if constexpr (ROWB > 0 && NW >= 4) redundancy_staged<ROWB, DT, PAD, NW, CW>(a, u, tbl, tmp, inv, (int *)(inv + rows), inv + 2 * rows, (char *)(inv + 3 * rows));
         } else {
             float *inv = tmp + a.T_max, *zv = tmp + 3 * (size_t)a.T_max;
             int *zr = (int *)(tmp + 2 * (size_t)a.T_max);

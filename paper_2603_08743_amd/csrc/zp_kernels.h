@@ -24,6 +24,7 @@ enum : int {
     EX_MOVE_F = 8,     // compaction moves F rows read back from global memory (staged call)
     EX_POOL_FIRST = 32,  // pooling only for requests without history
     EX_RED_FUSED = 64,   // redundancy: the similarity tiles of the live prefix come from the key tiles of sweep 2 (row sums at off_R)
+    EX_RED_STAGED = 128, // redundancy of large blocks: block by block, rows through LDS (redundancy_staged)
     EX_MOVE_F_LDS = 16 // compaction writes the kept entries' values from the on-chip copy made by EX_GLOBAL (fused call)
 };
 

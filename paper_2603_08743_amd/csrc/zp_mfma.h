@@ -253,7 +253,11 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             }
         }
     };
+    // Launches with redundancy may have more waves than query blocks (red_waves in zp_api.hip): a wave without a block leaves the arithmetic
+    // out; its sums of sweep 1 are never read, those of sweep 2 stay zero.
+    const bool idle = REF == 3 && RB == 1 && (pass * NW + __builtin_amdgcn_readfirstlane(wv)) * 2 * UL >= w;
     auto sweep1_tile = [&](const char *buf, int j0, bool fresh) __attribute__((always_inline)) {
+        if (idle) return;
         if (j0 + KT > u.Tv - w) sweep1_body(buf, j0, fresh, std::true_type());
         else sweep1_body(buf, j0, fresh, std::false_type());
     };
@@ -435,6 +439,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
         }
     };
     auto sweep2_tile = [&](const char *buf, float *pt, int j0) __attribute__((always_inline)) {
+        if (idle) return;
         if (j0 + KT > u.Tv - w) sweep2_body(buf, pt, j0, std::true_type());
         else sweep2_body(buf, pt, j0, std::false_type());
     };
@@ -455,6 +460,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             }
         }
     };
+    if (idle && lane < KT) part[wv * KT + lane] = part[(NW + wv) * KT + lane] = 0.f;
     // tiles are taken in DESCENDING order (tile number rt = t_hi-1-it): the keys sweep 1 read last are the ones
     // most likely to be still in L2 / Infinity Cache
     gload(t_hi - 1, SetA(), ZP_NT2());
