@@ -117,9 +117,9 @@ extern "C" zp_status zp_set_option(zp_ctx *ctx, int32_t option, int32_t value) {
 // (redundancy_staged) where a block has column groups of 32 for at least half the waves.  Fragments straight from L2 against this,
 // in us: paper geometry (two query blocks, blocks of 256, 1152 units of 2304) 1692:951, with two waves 1384; 512 units of 2176 in
 // blocks of 128 (one query block) 880:383; 512 units of 4160 in blocks of 64, four waves 1183:884; with eight waves blocks of 64 keep
-// two waves busy and stay with redundancy_blocks (1006:1028, the larger kernel).
+// two waves busy and stay with redundancy_blocks.
 static int red_waves(int b) { return b > 96 ? 8 : b > 32 ? 4 : 1; }
-static bool red_staged(int b, int NW) { return b > 32 && 2 * ((b + 31) / 32) >= NW; }
+static bool red_staged(int b, int NW) { return b > 32 && NW >= 4 && 2 * ((b + 31) / 32) >= NW; }
 
 // Scalar checks shared by every call, and the kernel argument block.  `need_q`: the call scores.
 static zp_status prepare(zp_ctx *ctx, const char *who, const zp_pool *p, const zp_batch *b, bool need_q, zp::Args *a,

@@ -1097,8 +1097,8 @@ __device__ __forceinline__ void block_row_sums(const Args &a, const Unit &u, con
 }
 
 // ROWB > 0: called from the matrix-core kernel for rows of up to ROWB bytes; ROWB = 0: generic kernel.  Element type DT.
-// REF 1: global score and pooling; REF 2: a launch whose similarity tiles came from sweep 2 (EX_RED_FUSED); REF 3: any other
-// with redundancy.
+// REF 1: global score and pooling; REF 2: a launch whose similarity tiles came from sweep 2 (EX_RED_FUSED); REF 4: redundancy of large
+// blocks (EX_RED_STAGED); REF 3: any other with redundancy.
 template <int ROWB, int DT, bool PAD, int REF, int NW, bool TIGHT>
 __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, const int *tbl, Misc *misc) {
     const int tid = threadIdx.x, nt = blockDim.x;
@@ -1141,13 +1141,13 @@ __device__ inline void refine_unit(const Args &a, const Unit &u, char *smem, con
         if constexpr (REF == 2) {                                // the live prefix was done from the key tiles of sweep 2
             tmp = (float *)(smem + a.off_R);
             redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, true);
-        } else if (ROWB > 0 && 32 % a.b == 0) {
-            if constexpr (ROWB > 0) redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, false);
-        } else if (ROWB > 0 && NW >= 4 && (a.ex & EX_RED_STAGED)) {
+        } else if constexpr (REF == 4) {
             const int rows = (a.b + 31) & ~31;
             float *inv = tmp + ((a.T_max + 3) & ~3);
             constexpr int CW = ROWB > 256 || TIGHT ? 1 : ROWB > 128 ? 2 : NW > 4 ? 1 : 4;
-            if constexpr (ROWB > 0 && NW >= 4) redundancy_staged<ROWB, DT, PAD, NW, CW>(a, u, tbl, tmp, inv, (int *)(inv + rows), inv + 2 * rows, (char *)(inv + 3 * rows));
+            redundancy_staged<ROWB, DT, PAD, NW, CW>(a, u, tbl, tmp, inv, (int *)(inv + rows), inv + 2 * rows, (char *)(inv + 3 * rows));
+        } else if (ROWB > 0 && 32 % a.b == 0) {
+            if constexpr (ROWB > 0) redundancy_mfma<ROWB, DT, PAD>(a, u, tbl, tmp, tmp + a.T_max, false);
         } else {
             float *inv = tmp + a.T_max, *zv = tmp + 3 * (size_t)a.T_max;
             int *zr = (int *)(tmp + 2 * (size_t)a.T_max);

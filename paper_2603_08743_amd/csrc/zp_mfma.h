@@ -49,7 +49,7 @@ template <int ROWB> struct KTile {
 
 // REF: 0 no score refinements in this launch, 1 global score and pooling in the tail, 3 the lightning redundancy as well, 2
 // (block size 16, RB = 1, unpadded bf16 rows) its similarity tiles of the live prefix taken from the key tiles of sweep 2
-// (with 3 the keys are read a third time in the tail).  With the redundancy code in it an eight-wave kernel has no registers
+// (with 3 the keys are read a third time in the tail), 4 the redundancy of large blocks (four and eight waves, redundancy_staged).  With the redundancy code in it an eight-wave kernel has no registers
 // left, so launches without redundancy do not carry it: 512 units of 4112 positions (d 128, G 4, w 64) with global score and
 // pooling took 644 us with 21 spilled registers and take 622 us with none.
 // MP: the query blocks take several passes over the keys (NP groups of NW * RB blocks), S collecting their sums.
@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     // up to 912 positions (G 5, w 11) 342 -> 338 us, 272 units of up to 1088 (d 64, w 34) 67.9 -> 65.3 us, 384 of 8208 (G 5, w 128) 1390 ->
     // 1380 us.  Not where the registers are full: 512 units of 4112 with the fused redundancy (REF 2) 659 -> 696 us, 80 units of 4288 with
     // the separate one 356 -> 361 us.
-    constexpr bool FIRST_MAX = REF < 2 || (REF == 3 && RB > 1);
+    constexpr bool FIRST_MAX = REF < 2 || (REF >= 3 && RB > 1);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int *tbl = (int *)(smem + a.off_tbl), *dst = (int *)(smem + a.off_dst);
     Misc *misc = (Misc *)(smem + a.off_misc);
@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     // the second set (DEEP) gives 3 % (160 units of 3440, G 4, w 72: 270 -> 262 us).  Loops of two tiles a turn (TWO) where a wave holds
     // several blocks (44 units of 9136, G 7, w 108: 508 -> 401 us) and with redundancy in the launch (448 units of 5200: 949 -> 921 us);
     // everywhere else one tile a turn is as fast, and one wave with two is four times slower.
-    constexpr bool TWO = RB > 1 || REF >= 2, DEEP = RB == 2 || (RB == 3 && REF != 3);
+    constexpr bool TWO = RB > 1 || REF >= 2, DEEP = RB == 2 || (RB == 3 && REF < 3);
     u32x4 stA[LPT], stB[LPT];                                 // named by type: passed by reference, the padded kernels take up to 180 registers more
     using SetA = std::false_type;
     using SetB = std::true_type;
@@ -253,9 +253,9 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             }
         }
     };
-    // Launches with redundancy may have more waves than query blocks (red_waves in zp_api.hip): a wave without a block leaves the arithmetic
-    // out; its sums of sweep 1 are never read, those of sweep 2 stay zero.
-    const bool idle = REF == 3 && RB == 1 && (pass * NW + __builtin_amdgcn_readfirstlane(wv)) * 2 * UL >= w;
+    // Launches with redundancy in large blocks may have more waves than query blocks (red_waves in zp_api.hip), padded rows have two waves
+    // at least: a wave without a block leaves the arithmetic out; its sums of sweep 1 are never read, those of sweep 2 stay zero.
+    const bool idle = (REF == 4 || (PAD && NW == 2)) && RB == 1 && (pass * NW + __builtin_amdgcn_readfirstlane(wv)) * 2 * UL >= w;
     auto sweep1_tile = [&](const char *buf, int j0, bool fresh) __attribute__((always_inline)) {
         if (idle) return;
         if (j0 + KT > u.Tv - w) sweep1_body(buf, j0, fresh, std::true_type());
@@ -519,12 +519,13 @@ static hipError_t launch_one(const Args &a, int units, hipStream_t s) {
     return hipGetLastError();
 }
 
-// ALL_REF: the refinement variants of a geometry (REF 1, 3, and 2 where it exists); otherwise the plain one
+// ALL_REF: the refinement variants of a geometry (REF 1, 3, and 2 and 4 where they exist); otherwise the plain one
 template <int ROWB, int RB, int NW, int GT, bool ALL_REF>
 static hipError_t launch_ref(const Args &a, int units, hipStream_t s) {
     if constexpr (!ALL_REF) return launch_one<1, ROWB, false, RB, NW, GT, 0, false>(a, units, s);
     else {
         if constexpr (RB == 1) if (a.ex & EX_RED_FUSED) return launch_one<1, ROWB, false, RB, NW, GT, 2, false>(a, units, s);
+        if constexpr (NW >= 4) if (a.ex & EX_RED_STAGED) return launch_one<1, ROWB, false, RB, NW, GT, 4, false>(a, units, s);
         if (a.ex & EX_RED) return launch_one<1, ROWB, false, RB, NW, GT, 3, false>(a, units, s);
         return launch_one<1, ROWB, false, RB, NW, GT, 1, false>(a, units, s);
     }
@@ -563,6 +564,8 @@ template <int DT, int ROWB>
 static hipError_t launch_pad(const Args &a, int units, int NW, hipStream_t s) {
     const bool ref = (a.ex & (EX_GLOBAL | EX_POOL | EX_RED)) != 0;
     if (NW == 2) return ref ? launch_one<DT, ROWB, true, 1, 2, 0, 3, false>(a, units, s) : launch_one<DT, ROWB, true, 1, 2, 0, 0, false>(a, units, s);
+    if (NW == 4 && (a.ex & EX_RED_STAGED)) return launch_one<DT, ROWB, true, 1, 4, 0, 4, false>(a, units, s);
+    if (NW == 8 && (a.ex & EX_RED_STAGED)) return launch_one<DT, ROWB, true, 1, 8, 0, 4, true>(a, units, s);
     if (NW == 4) return ref ? launch_one<DT, ROWB, true, 1, 4, 0, 3, false>(a, units, s) : launch_one<DT, ROWB, true, 1, 4, 0, 0, false>(a, units, s);
     if (NW == 8) return ref ? launch_one<DT, ROWB, true, 1, 8, 0, 3, true>(a, units, s) : launch_one<DT, ROWB, true, 1, 8, 0, 0, true>(a, units, s);
     return hipErrorInvalidConfiguration;
