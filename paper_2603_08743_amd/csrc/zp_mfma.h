@@ -18,9 +18,8 @@ namespace zp {
 // vector-ALU phases of different waves and gives the row-moving phase sixteen waves per CU to issue memory operations
 // from (measured on the 8B-like shape: 15.0 ms per launch against 17.0 ms with four waves of two blocks each).
 // Rows above 256 bytes keep 8 more registers of query fragments per 64 bytes, and as many again of tile loads: half the waves.
-// Padded rows of 192 and 256 bytes with eight waves and 1024-byte rows with four spill at these targets (29 to 54, and 83 to 127
-// registers).  With half the waves and no spills 128 units of 1040 positions are faster (d 96, w 64 95 -> 89 us; fp32 d 256, w 32 465 ->
-// 426), 512 units slower (180 -> 207; 1040 -> 1162; refined bf16 d 512 679 -> 845): the second workgroup per compute unit is worth more.
+// Below four waves the compiler is left its own choice: held to 168 registers, one-wave kernels of 256-byte rows take 30 % longer (1344
+// units of 3760 positions, G 1, w 32: 1449 -> 1900 us) and two-wave kernels of 512-byte rows spill hundreds of registers.
 #define ZP_WPE(NW, RB, ROWB) ((NW) == 8 && (RB) == 1 && (ROWB) <= 256 ? 4 : ((NW) >= 4 ? 2 : 1))
 
 // ------------------------------------------------------------------ matrix-core path
@@ -129,7 +128,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
     // positions and cost up to 130 registers.  With two or three blocks per wave one workgroup has the compute unit to itself and
     // the second set (DEEP) gives 3 % (160 units of 3440, G 4, w 72: 270 -> 262 us).  Loops of two tiles a turn (TWO) where a wave holds
     // several blocks (44 units of 9136, G 7, w 108: 508 -> 401 us) and with redundancy in the launch (448 units of 5200: 949 -> 921 us);
-    // everywhere else one tile a turn is as fast, and one wave with two is four times slower.
+    // everywhere else two tiles a turn change nothing (182 calls of all kinds: 1.001 times) and cost code.
     constexpr bool TWO = RB > 1 || REF >= 2, DEEP = RB == 2 || (RB == 3 && REF < 3);
     u32x4 stA[LPT], stB[LPT];                                 // named by type: passed by reference, the padded kernels take up to 180 registers more
     using SetA = std::false_type;
@@ -253,9 +252,9 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ZP
             }
         }
     };
-    // Launches with redundancy in large blocks may have more waves than query blocks (red_waves in zp_api.hip), padded rows have two waves
-    // at least: a wave without a block leaves the arithmetic out; its sums of sweep 1 are never read, those of sweep 2 stay zero.
-    const bool idle = (REF == 4 || (PAD && NW == 2)) && RB == 1 && (pass * NW + __builtin_amdgcn_readfirstlane(wv)) * 2 * UL >= w;
+    // Launches with redundancy in large blocks may have more waves than query blocks (red_waves in zp_api.hip), padded rows take
+    // two, four or eight waves: a wave without a block leaves the arithmetic out; its sums of sweep 1 are never read, those of sweep 2 stay zero.
+    const bool idle = (REF == 4 || PAD) && RB == 1 && (pass * NW + __builtin_amdgcn_readfirstlane(wv)) * 2 * UL >= w;
     auto sweep1_tile = [&](const char *buf, int j0, bool fresh) __attribute__((always_inline)) {
         if (idle) return;
         if (j0 + KT > u.Tv - w) sweep1_body(buf, j0, fresh, std::true_type());
